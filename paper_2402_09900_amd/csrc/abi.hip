@@ -69,7 +69,7 @@ uint64_t layout_sig(std::initializer_list<int64_t> vals) {
 
 // entry points in a signature
 enum SigKind : int64_t { kSigDiag = 1, kSigDiagBwd, kSigFfm, kSigFfmBwd, kSigDiscount, kSigTbbBegins,
-                         kSigLinattn, kSigLinattnBwd, kSigTbbSample };
+                         kSigTbbSample };
 
 // Tiling and workspace layout of a diagonal scan.  `vec` selects the
 // vectorised lane width; `state_complex` picks the descriptor size.
@@ -653,49 +653,85 @@ int memoroid_scan_diag_bwd_prepared(const void* a, int64_t a_stride_t, const uin
 }
 
 // ---------------------------------------------------------- linear attention
-// Summaries per (chunk, head) -> resettable sum-scan of the chunk states over
-// chunks (the diagonal scan with a = 1, the monoid of App. G.1 being a sum)
-// -> outputs per (chunk, head).
+// Summaries per (segment, head) -> resettable sum-scan of the segment states
+// (the monoid of App. G.1 is a sum) -> outputs per (segment, head).
 
 namespace {
 
+// 64-row chunks per segment (1, 2, 4 or 8).  A workgroup walks a segment, so
+// longer segments write and read fewer states (16.6 KB each) but leave fewer
+// workgroups: a segment doubles as long as MEMOROID_LIN_MIN_GROUPS remain, two
+// per CU (forward / gradient in us with at least 256, 512 and 1024 workgroups:
+// T = 32768, 4 heads 71 / 166, 64 / 152, 67 / 164; T = 16384 42 / 94, 42 / 92,
+// 44 / 104; T = 49152, 8 heads 157 / 414, 157 / 413, 167 / 420).
+#ifndef MEMOROID_LIN_MIN_GROUPS
+#define MEMOROID_LIN_MIN_GROUPS 512
+#endif
+int lin_chunks(int64_t T, int64_t H) {
+    const int64_t n = (T + kLinChunkRows - 1) / kLinChunkRows;
+    int c = 1;
+    while (c < 8 && (n + 2 * c - 1) / (2 * c) * H >= MEMOROID_LIN_MIN_GROUPS) c *= 2;
+    return c;
+}
+
 struct LinPlan {
-    int64_t nch = 0, dstate = 0;
-    size_t off_dS = 0, off_Sinc = 0, off_R = 0, off_scan = 0, off_cnt = 0, total = 0;
-    DiagPlan scan;
+    int chunks = 1;
+    int64_t nseg = 0, width = 0;
+    size_t off_cnt = 0, off_states = 0, off_R = 0, total = 0;
 };
 
+// heads of one call: a bound on the state row (kLinStateWords floats a head)
+constexpr int64_t kLinMaxHeads = 251;
+
 bool plan_linattn(int64_t T, int64_t H, LinPlan* p) {
-    p->nch = (T + kLinChunk - 1) / kLinChunk;
-    p->dstate = H * kLinStateWords;
-    const size_t states = (size_t)p->nch * (size_t)p->dstate * 4;
-    // the state scan's own workspace comes first, so that its header (and
-    // timeout word) sits at offset 0 like every other call's; the chunk
-    // begin-count words follow its descriptors so one fill covers both
-    size_t off = 0;
-    p->off_scan = off;
-    // the state scan always runs vectorised: dstate % 4 == 0 and every
-    // buffer is 256-byte aligned inside the workspace
-    if (!plan_diag(1, p->nch, p->dstate, MEMOROID_F32, true, diag_rows(false, true), false, true, false, &p->scan))
-        return false;
-    off = align_up(off + p->scan.total);
-    p->off_cnt = off;
-    off = align_up(off + (size_t)p->nch * 8);
-    p->off_dS = off;
-    off = align_up(off + states);
-    p->off_Sinc = off;
-    off = align_up(off + states);
+    if (H > kLinMaxHeads) return false;
+    p->chunks = lin_chunks(T, H);
+    const int64_t rows = (int64_t)p->chunks * kLinChunkRows;
+    p->nseg = (T + rows - 1) / rows;
+    p->width = H * kLinStateWords;
+    size_t off = kAlign;                                   // header (timeout word)
+    p->off_cnt = off;                                      // begin-count words, filled with the header
+    off = align_up(off + (size_t)p->nseg * 8);
+    p->off_states = off;
+    off = align_up(off + (size_t)p->nseg * (size_t)p->width * 4);
     p->off_R = off;
-    off = align_up(off + (size_t)p->nch);
+    off = align_up(off + (size_t)p->nseg);
     p->total = off;
     return true;
+}
+
+// Extents the kernels address: 32-bit offsets inside a block's rows, the grid.
+bool lin_extents_ok(int64_t T, int64_t H) { return T <= (int64_t)INT32_MAX / 2 && H <= 65535; }
+
+// Forward states of every segment, scanned, with the workspace's header and
+// count words prepared.
+int lin_states(const float* k, const float* v, const uint8_t* start, int64_t T, int64_t H, const LinPlan& p, char* ws,
+               hipStream_t s) {
+    LinSummaryArgs sa{};
+    sa.k = k;
+    sa.v = v;
+    sa.start = start;
+    sa.states = (float*)(ws + p.off_states);
+    sa.R = (uint8_t*)(ws + p.off_R);
+    sa.T = T;
+    sa.H = H;
+    sa.chunks = p.chunks;
+    sa.fill = (u32x4*)ws;
+    sa.fill16 = (int64_t)(p.off_states / 16);
+    if (linattn_summary_launch(sa, p.nseg, s) != hipSuccess) return MEMOROID_EHIP;
+    LinScanArgs ca{};
+    ca.states = sa.states;
+    ca.R = sa.R;
+    ca.n = p.nseg;
+    ca.width = p.width;
+    return check_hip(linattn_scan_launch(false, ca, s));
 }
 
 }  // namespace
 
 size_t memoroid_scan_linattn_workspace_bytes(int64_t T, int64_t H, int64_t dk, int64_t dv, int64_t chunk) {
     if (T <= 0 || H <= 0 || dk != 64 || dv != 64 || chunk != 64) return 0;
-    if (T > (int64_t)INT32_MAX / 2 || H > 65535) return 0;
+    if (!lin_extents_ok(T, H)) return 0;
     LinPlan p;
     if (!plan_linattn(T, H, &p)) return 0;
     return p.total;
@@ -707,7 +743,7 @@ int memoroid_scan_linattn(const float* q, const float* k, const float* v, const 
     if (T < 0 || H < 0 || dk < 0 || dv < 0 || chunk < 0) return MEMOROID_EINVAL;
     if (dk != 64 || dv != 64 || chunk != 64) return MEMOROID_EUNSUPPORTED;
     if (T == 0 || H == 0) return MEMOROID_OK;
-    if (T > (int64_t)INT32_MAX / 2 || H > 65535) return MEMOROID_EUNSUPPORTED;
+    if (!lin_extents_ok(T, H)) return MEMOROID_EUNSUPPORTED;
     if (!q || !k || !v || !start || !out) return MEMOROID_EINVAL;
     if (!aligned(q, 16) || !aligned(k, 16) || !aligned(v, 16) || !aligned(out, 16) ||
         (episode_idx && !aligned(episode_idx, 4)))
@@ -722,51 +758,22 @@ int memoroid_scan_linattn(const float* q, const float* k, const float* v, const 
     if (!aligned(workspace, 256)) return MEMOROID_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
-    char* sw = ws + p.off_scan;
-    float* dS = (float*)(ws + p.off_dS);
-    float* Sinc = (float*)(ws + p.off_Sinc);
-    uint8_t* R = (uint8_t*)(ws + p.off_R);
-    LinSummaryArgs sa{};
-    sa.k = k;
-    sa.v = v;
-    sa.start = start;
-    sa.dS = dS;
-    sa.R = R;
-    sa.T = T;
-    sa.H = H;
-    // the summary kernel prepares the state scan's workspace and the count
-    // words (one contiguous run from offset 0) on every call
-    sa.fill = (u32x4*)sw;
-    sa.fill16 = (int64_t)((p.off_cnt + (size_t)p.nch * 8 - p.off_scan + 15) / 16);
-    if (linattn_summary_launch(sa, s) != hipSuccess) return MEMOROID_EHIP;
-    DiagFwdArgs args{};
-    args.a = nullptr;            // a = 1: the state scan is a resettable sum
-    args.x = dS;
-    args.start = R;
-    args.h = Sinc;
-    args.T = p.nch;
-    args.d = p.dstate;
-    args.Qp = p.scan.Qp;
-    args.nfb = p.scan.nfb;
-    args.nchains = (int32_t)p.scan.nchains;
-    set_scan_ws(args, p.scan, sw, (WsHeader*)sw, layout_sig({kSigLinattn, T, H}));
-    args.idx = nullptr;
-    args.cnt = nullptr;
-    if (diag_fwd_launch(K_F32, K_F32, true, true, args, p.scan.ntiles, s) != hipSuccess) return MEMOROID_EHIP;
+    const int st = lin_states(k, v, start, T, H, p, ws, s);
+    if (st != MEMOROID_OK) return st;
     LinOutputArgs oa{};
     oa.q = q;
     oa.k = k;
     oa.v = v;
     oa.start = start;
-    oa.Sinc = Sinc;
+    oa.states = (const float*)(ws + p.off_states);
     oa.out = out;
     oa.T = T;
     oa.H = H;
+    oa.chunks = p.chunks;
     oa.idx = episode_idx;
     oa.cnt = (uint64_t*)(ws + p.off_cnt);
-    oa.timeout = &((WsHeader*)sw)->timeout;
-    if (linattn_output_launch(oa, s) != hipSuccess) return MEMOROID_EHIP;
-    return MEMOROID_OK;
+    oa.timeout = &((WsHeader*)ws)->timeout;
+    return check_hip(linattn_output_launch(oa, p.nseg, s));
 }
 
 // ------------------------------------------------- linear attention, grad
@@ -774,30 +781,19 @@ int memoroid_scan_linattn(const float* q, const float* k, const float* v, const 
 namespace {
 
 struct LinBwdPlan {
-    LinPlan fwd;                 // the forward summaries and state scan, from offset 0
-    DiagPlan rscan;              // the reverse chunk-state scan
-    size_t off_dnum = 0, off_dden = 0, off_dU = 0, off_Y = 0, off_Rs = 0, off_rscan = 0, total = 0;
+    LinPlan fwd;                 // the forward states, from offset 0
+    size_t off_rden = 0, off_dden = 0, off_rstates = 0, total = 0;
 };
 
 bool plan_linattn_bwd(int64_t T, int64_t H, LinBwdPlan* p) {
     if (!plan_linattn(T, H, &p->fwd)) return false;
-    const int64_t nch = p->fwd.nch;
-    const size_t states = (size_t)nch * (size_t)p->fwd.dstate * 4;
-    size_t off = align_up(p->fwd.total);
-    p->off_dnum = off;
-    off = align_up(off + (size_t)T * (size_t)H * kLinChunk * 4);
+    size_t off = p->fwd.total;
+    p->off_rden = off;
+    off = align_up(off + (size_t)T * (size_t)H * 4);
     p->off_dden = off;
     off = align_up(off + (size_t)T * (size_t)H * 4);
-    p->off_dU = off;
-    off = align_up(off + states);
-    p->off_Y = off;
-    off = align_up(off + states);
-    p->off_Rs = off;
-    off = align_up(off + (size_t)nch);
-    if (!plan_diag(1, nch, p->fwd.dstate, MEMOROID_F32, true, diag_rows(true, true), true, true, false, &p->rscan))
-        return false;
-    p->off_rscan = off;
-    off = align_up(off + p->rscan.total);
+    p->off_rstates = off;
+    off = align_up(off + (size_t)p->fwd.nseg * (size_t)p->fwd.width * 4);
     p->total = off;
     return true;
 }
@@ -806,7 +802,7 @@ bool plan_linattn_bwd(int64_t T, int64_t H, LinBwdPlan* p) {
 
 size_t memoroid_scan_linattn_bwd_workspace_bytes(int64_t T, int64_t H, int64_t dk, int64_t dv, int64_t chunk) {
     if (T <= 0 || H <= 0 || dk != 64 || dv != 64 || chunk != 64) return 0;
-    if (T > (int64_t)INT32_MAX / 2 || H > 65535) return 0;
+    if (!lin_extents_ok(T, H)) return 0;
     LinBwdPlan p;
     if (!plan_linattn_bwd(T, H, &p)) return 0;
     return p.total;
@@ -819,7 +815,7 @@ int memoroid_scan_linattn_bwd(const float* q, const float* k, const float* v, co
     if (T < 0 || H < 0 || dk < 0 || dv < 0 || chunk < 0) return MEMOROID_EINVAL;
     if (dk != 64 || dv != 64 || chunk != 64) return MEMOROID_EUNSUPPORTED;
     if (T == 0 || H == 0) return MEMOROID_OK;
-    if (T > (int64_t)INT32_MAX / 2 || H > 65535) return MEMOROID_EUNSUPPORTED;
+    if (!lin_extents_ok(T, H)) return MEMOROID_EUNSUPPORTED;
     const float* ins[6] = {q, k, v, out, grad_out, nullptr};
     float* outs[3] = {grad_q, grad_k, grad_v};
     for (int i = 0; i < 5; ++i)
@@ -839,39 +835,11 @@ int memoroid_scan_linattn_bwd(const float* q, const float* k, const float* v, co
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
     const LinPlan& f = p.fwd;
-    char* sw = ws + f.off_scan;
-    float* dS = (float*)(ws + f.off_dS);
-    float* Sinc = (float*)(ws + f.off_Sinc);
-    uint8_t* R = (uint8_t*)(ws + f.off_R);
 
-    // forward chunk states (as in the forward pass, without the readout)
-    LinSummaryArgs sa{};
-    sa.k = k;
-    sa.v = v;
-    sa.start = start;
-    sa.dS = dS;
-    sa.R = R;
-    sa.T = T;
-    sa.H = H;
-    sa.fill = (u32x4*)sw;
-    sa.fill16 = (int64_t)((f.off_cnt + (size_t)f.nch * 8 - f.off_scan + 15) / 16);
-    if (linattn_summary_launch(sa, s) != hipSuccess) return MEMOROID_EHIP;
-    const uint64_t sig = layout_sig({kSigLinattnBwd, T, H});
-    DiagFwdArgs fa{};
-    fa.a = nullptr;
-    fa.x = dS;
-    fa.start = R;
-    fa.h = Sinc;
-    fa.T = f.nch;
-    fa.d = f.dstate;
-    fa.Qp = f.scan.Qp;
-    fa.nfb = f.scan.nfb;
-    fa.nchains = (int32_t)f.scan.nchains;
-    set_scan_ws(fa, f.scan, sw, (WsHeader*)sw, sig);
-    if (diag_fwd_launch(K_F32, K_F32, true, true, fa, f.scan.ntiles, s) != hipSuccess) return MEMOROID_EHIP;
+    // forward segment states (as in the forward pass, without the readout)
+    const int st = lin_states(k, v, start, T, H, f, ws, s);
+    if (st != MEMOROID_OK) return st;
 
-    // backward summaries (and the reverse scan's workspace set-up)
-    char* rw = ws + p.off_rscan;
     LinBwdArgs ba{};
     ba.q = q;
     ba.k = k;
@@ -879,42 +847,28 @@ int memoroid_scan_linattn_bwd(const float* q, const float* k, const float* v, co
     ba.out = out;
     ba.g = grad_out;
     ba.start = start;
-    ba.Sinc = Sinc;
-    ba.dnum = (float*)(ws + p.off_dnum);
+    ba.states = (const float*)(ws + f.off_states);
+    ba.rstates = (float*)(ws + p.off_rstates);
+    ba.rden = (float*)(ws + p.off_rden);
     ba.dden = (float*)(ws + p.off_dden);
-    ba.dU = (float*)(ws + p.off_dU);
-    ba.Rs = (uint8_t*)(ws + p.off_Rs);
-    ba.Y = (const float*)(ws + p.off_Y);
     ba.dq = grad_q;
     ba.dk = grad_k;
     ba.dv = grad_v;
     ba.T = T;
     ba.H = H;
-    ba.nch = f.nch;
-    ba.fill = (u32x4*)rw;
-    ba.fill16 = (int64_t)(p.rscan.total / 16);
-    if (linattn_bwd_summary_launch(ba, s) != hipSuccess) return MEMOROID_EHIP;
+    ba.nseg = f.nseg;
+    ba.chunks = f.chunks;
+    if (linattn_dq_launch(ba, s) != hipSuccess) return MEMOROID_EHIP;
 
-    // reverse chunk-state scan: Y_c = dU_c + [chunk c holds no begin] Y_{c+1}
-    // (the reverse diagonal scan with a = 1, cut by the shifted chunk flags);
-    // a wait that gives up flags the timeout word of the forward header
-    DiagBwdArgs ra{};
-    ra.a = nullptr;
-    ra.start = ba.Rs;
-    ra.h = nullptr;
-    ra.g = ba.dU;
-    ra.dx = (void*)ba.Y;
-    ra.da = nullptr;
-    ra.da_part = nullptr;
-    ra.T = f.nch;
-    ra.d = f.dstate;
-    ra.Qp = p.rscan.Qp;
-    ra.nfb = p.rscan.nfb;
-    ra.nchains = (int32_t)p.rscan.nchains;
-    set_scan_ws(ra, p.rscan, rw, (WsHeader*)sw, sig);
-    if (diag_bwd_launch(K_F32, true, true, ra, p.rscan.ntiles, s) != hipSuccess) return MEMOROID_EHIP;
-
-    return check_hip(linattn_bwd_grad_launch(ba, s));
+    // scan of the reverse summaries: Y_c = dU_c + [segment c holds no begin
+    // step] Y_{c+1}
+    LinScanArgs ca{};
+    ca.states = ba.rstates;
+    ca.R = (const uint8_t*)(ws + f.off_R);
+    ca.n = f.nseg;
+    ca.width = f.width;
+    if (linattn_scan_launch(true, ca, s) != hipSuccess) return MEMOROID_EHIP;
+    return check_hip(linattn_dkv_launch(ba, s));
 }
 
 // ------------------------------------------------------------------ status

@@ -159,13 +159,10 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
             for (int v = 0; v < VEC; ++v) ainv[v] = sFfm[q * VEC + v];
         }
     } else if constexpr (AINV) {
-        // a NULL time-invariant a stands for a = 1 (the reverse sum, used by
-        // the linear-attention gradient's state scan)
         RawVec<K, VEC> r0;
-        const bool have = active && p.a != nullptr;
-        if (have) raw_load(r0, (const char*)p.a + f0 * EB);
+        if (active) raw_load(r0, (const char*)p.a + f0 * EB);
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) ainv[v] = have ? conj(C::get(r0, v)) : s_one<S>();
+        for (int v = 0; v < VEC; ++v) ainv[v] = active ? conj(C::get(r0, v)) : s_one<S>();
     }
     auto coef = [&](int r, int v) -> S {      // conj(a_{t+1})
         if constexpr (AINV) return ainv[v];

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
     const int64_t bidle = p.bank - boff;
     void* const agg = (char*)p.agg + boff;
     void* const incl = (char*)p.incl + boff;
-    uint64_t* const cnt = p.cnt ? (uint64_t*)((char*)p.cnt + boff) : nullptr;
+    uint64_t* const cnt = (uint64_t*)((char*)p.cnt + boff);
     const int b = chain / p.nfb;
     const int fb = chain - b * p.nfb;
     const int Qp = p.Qp;
@@ -218,13 +218,10 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
             for (int v = 0; v < VEC; ++v) ainv[v] = sFfm[q * VEC + v];
         }
     } else if constexpr (AINV) {
-        // a NULL time-invariant a stands for a = 1 (the sum monoid, used by
-        // the linear-attention state scan)
         RawVec<IN, VEC> r0;
-        const bool have = active && p.a != nullptr;
-        if (have) raw_load(r0, (const char*)p.a + f0 * IB);
+        if (active) raw_load(r0, (const char*)p.a + f0 * IB);
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) ainv[v] = have ? CIn::get(r0, v) : s_one<S>();
+        for (int v = 0; v < VEC; ++v) ainv[v] = active ? CIn::get(r0, v) : s_one<S>();
     }
     auto a_at = [&](int r, int v) -> S {
         if constexpr (AINV) return ainv[v];
@@ -322,7 +319,7 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
                 Desc<S>::clear((char*)p.agg + bidle, (char*)p.incl + bidle, desc_slot(ticket, Dp, Qp, q, v));
         }
         // the count word of the idle bank, whether or not this call counts
-        if (p.cnt != nullptr && fb == 0 && lane == 0)
+        if (fb == 0 && lane == 0)
             ((uint64_t*)((char*)p.cnt + bidle))[tile * (p.nchains / p.nfb) + b] = kEmpty64;
     }
     uint32_t c_before = 0, c_tile = 0;           // begins before this wavefront / in the tile

@@ -15,9 +15,7 @@ struct WsHeader;
 // 256 / Qp * rows steps long: 64 for full-width feature blocks).  The reverse
 // scan with a per-step a keeps three tensors per step (g, a, h) and so holds
 // fewer steps, to stay within 256 registers (two workgroups per CU); with a
-// time-invariant a it runs 8 (shorter tiles, more of them in flight: the
-// linear-attention state scan, one tile per chain at 16, took 21.2 µs
-// against 18.5 at 8).
+// time-invariant a it runs 8 (shorter tiles, more of them in flight).
 #ifndef MEMOROID_FWD_ROWS
 #define MEMOROID_FWD_ROWS 16
 #endif
@@ -95,7 +93,7 @@ struct DiagFwdArgs {
     // descriptor words, bank 0 (bank 1 lies `bank` bytes further on)
     void* agg;         // [tiles][Dp] aggregate descriptor words
     void* incl;        // [tiles][Dp] inclusive-prefix descriptor words
-    uint64_t* cnt;     // [tiles per chain][B] begin-count descriptor words, or NULL
+    uint64_t* cnt;     // [tiles per chain][B] begin-count descriptor words
     int64_t bank;
     WsHeader* hdr;
     uint64_t sig;      // signature of the call (workspace binding)
@@ -178,22 +176,30 @@ constexpr int kCtrStride = 32;
 hipError_t ws_init_launch(void* zero, size_t zero_bytes, void* ones, size_t ones_bytes, hipStream_t s);
 hipError_t store_i64_launch(int64_t* p, int64_t v, hipStream_t s);
 
-// Linear-attention memoroid: per-(chunk, head) state summaries, and outputs
-// from the scanned chunk states.  A state is S^T (64x64, row n holds column n
-// of S) followed by z (64), kLinStateWords floats.
-constexpr int kLinChunk = 64;
+// Linear-attention memoroid.  The tape is cut into segments of `chunks`
+// 64-row chunks; a state is S (64x64, row-major) followed by z (64),
+// kLinStateWords floats, one per (segment, head).
+constexpr int kLinChunkRows = 64;
 constexpr int kLinStateWords = 64 * 64 + 64;
 
 struct LinSummaryArgs {
     const float* k;
     const float* v;
     const uint8_t* start;
-    float* dS;          // [chunks][H][kLinStateWords]
-    uint8_t* R;         // [chunks] chunk holds a begin step
+    float* states;      // [segments][H][kLinStateWords]
+    uint8_t* R;         // [segments] segment holds a begin step
     int64_t T;
     int64_t H;
-    u32x4* fill;        // state-scan workspace to prepare (all-ones bytes, 16-byte units)
+    int32_t chunks;
+    u32x4* fill;        // header and count words to prepare (all-ones bytes, 16-byte units)
     int64_t fill16;
+};
+
+struct LinScanArgs {
+    float* states;      // [n][width], scanned in place
+    const uint8_t* R;   // [n] reset flags
+    int64_t n;          // segments
+    int64_t width;      // floats per segment: H * kLinStateWords
 };
 
 struct LinOutputArgs {
@@ -201,41 +207,40 @@ struct LinOutputArgs {
     const float* k;
     const float* v;
     const uint8_t* start;
-    const float* Sinc;  // scanned states, [chunks][H][kLinStateWords]
+    const float* states;   // scanned states, [segments][H][kLinStateWords]
     float* out;
     int64_t T;
     int64_t H;
+    int32_t chunks;
     int32_t* idx;       // episode index out [T], or NULL
-    uint64_t* cnt;      // [chunks] begin-count words (filled by the summary kernel)
+    uint64_t* cnt;      // [segments] begin-count words (filled by the summary kernel)
     uint32_t* timeout;
 };
 
-hipError_t linattn_summary_launch(const LinSummaryArgs& a, hipStream_t s);
-hipError_t linattn_output_launch(const LinOutputArgs& a, hipStream_t s);
+hipError_t linattn_summary_launch(const LinSummaryArgs& a, int64_t nseg, hipStream_t s);
+hipError_t linattn_scan_launch(bool rev, const LinScanArgs& a, hipStream_t s);
+hipError_t linattn_output_launch(const LinOutputArgs& a, int64_t nseg, hipStream_t s);
 
 struct LinBwdArgs {
     const float* q;
     const float* k;
     const float* v;
-    const float* out;   // forward readout [T][H][64]
-    const float* g;     // dL/dout [T][H][64]
+    const float* out;      // forward readout [T][H][64]
+    const float* g;        // dL/dout [T][H][64]
     const uint8_t* start;
-    const float* Sinc;  // forward chunk states after each chunk [chunks][H][kLinStateWords]
-    float* dnum;        // workspace [T][H][64]
-    float* dden;        // workspace [T][H]
-    float* dU;          // reverse chunk summaries [chunks][H][kLinStateWords] (U [kd][n], then w)
-    uint8_t* Rs;        // [chunks] reverse-scan flags: Rs[c] = chunk c - 1 holds a begin
-    const float* Y;     // reverse-scanned states [chunks][H][kLinStateWords]
+    const float* states;   // scanned forward states
+    float* rstates;        // reverse summaries, scanned in between
+    float* rden;           // workspace [T][H]
+    float* dden;           // workspace [T][H]
     float* dq;
     float* dk;
     float* dv;
-    int64_t T, H, nch;
-    u32x4* fill;        // reverse-scan workspace to prepare (all-ones bytes)
-    int64_t fill16;
+    int64_t T, H, nseg;
+    int32_t chunks;
 };
 
-hipError_t linattn_bwd_summary_launch(const LinBwdArgs& a, hipStream_t s);
-hipError_t linattn_bwd_grad_launch(const LinBwdArgs& a, hipStream_t s);
+hipError_t linattn_dq_launch(const LinBwdArgs& a, hipStream_t s);
+hipError_t linattn_dkv_launch(const LinBwdArgs& a, hipStream_t s);
 
 // ------------------------------------------- discounted return and GAE
 // Steps per lane: 32 for the return (two streams in registers), 16 for the

@@ -1,299 +1,365 @@
-// linattn.hip -- chunked kernels of the linear-transformer memoroid (App. G.1)
-// over a tape with resets, for gfx950.
+// linattn.hip -- kernels of the linear-transformer memoroid (App. G.1) over a
+// tape with resets, for gfx950.
 //
 // The memoroid's monoid is a plain sum, (S, z) . (S', z') = (S + S', z + z'),
 // of outer products phi(k) v^T and of phi(k); under the reset transform the
-// state of step t sums only the steps of t's episode up to t.  Chunks of C = 64
-// steps are processed as dense 64x64x64 contractions on the fp32 matrix cores:
+// state of step t sums only the steps of t's episode up to t.  The tape is cut
+// into segments of a few 64-row chunks (lin_chunks in abi.hip), and a workgroup
+// takes one segment of one head:
 //
-//   summary kernel (one workgroup per chunk and head):
-//     dS^T = V^T phi(K)  over the rows after the chunk's last begin step
-//     dz   = column sums of those phi(K) rows;  R = "chunk holds a begin"
-//     (it also initialises the state scan's workspace);
-//   the chunk states are then scanned with the resettable diagonal scan
-//   (a = 1: the sum monoid), giving S_inc(c) = state after chunk c;
-//   output kernel (one workgroup per chunk and head), with r_i the last begin
-//   step <= i inside the chunk (-1 if none):
-//     A   = phi(Q) phi(K)^T,  masked to j <= i and j >= r_i
-//     num = A V + [r_i < 0] phi(Q) S_inc(c-1),  den = rowsum(A) + [r_i < 0] phi(Q).z
-//     out = num / den;
-//   the head-0 workgroups also produce the episode index of the chunk's steps.
+//   summary kernel: dS = sum of phi(k) v^T and dz = sum of phi(k) over the
+//     rows from the segment's last begin step on; R = "segment holds a begin";
+//   state scan: the segment states are scanned with resets, in place, giving
+//     the state after every segment;
+//   output kernel: walks the segment's chunks with the state in registers.
+//     Per 16-row block, with first(i) the first row of row i's episode in the
+//     block and the state taking part only in rows before the block's first
+//     begin:
+//       A   = phi(Q) phi(K)^T,  masked to first(i) <= j <= i
+//       out = (A V + phi(Q) S) / (rowsum(A) + phi(Q) z)
+//     and S += phi(K)^T V, z += sum phi(K) over the rows from the last begin;
+//     the head-0 workgroups also produce the episode index of their steps.
 //
-// Contractions use v_mfma_f32_16x16x4_f32 on operands staged in LDS in their
-// natural (row-major) layout.  In one MFMA the four k-slots take k = 16*slot
-// + s, a permutation of the contraction index applied to both operands, so
-// an operand stored with k contiguous is read with 16-byte LDS loads; one
-// stored with k as its row index is read with 4-byte loads whose rows are
-// rotated by 16 columns per 16 rows, which spreads the four k-slots over
-// different LDS banks.
+// Blocks of 16 rows do fewer flops than whole 64-row chunks would (the causal
+// product costs 16 columns a row instead of 40), and a segment of several
+// chunks writes and reads fewer states (16.6 KB each).  See linattn_common.hpp
+// for the layouts that let a block's products and the state meet in registers.
+//
+// Measured against one workgroup per 64-row chunk with every chunk's state
+// through memory and a look-back scan over them (T = 32768, 4 heads): forward
+// 74 -> 64 us (summary 23 -> 19, scan 15 -> 6.3, output 41 -> 41), gradient
+// 198 -> 152 us; T = 1000: 22 -> 19 and 45 -> 37 us.
 #include "linattn_common.hpp"
 
 namespace memoroid {
 
 // ---------------------------------------------------------------- summaries
-
-__global__ __launch_bounds__(256) void linattn_summary_kernel(LinSummaryArgs p) {
-    __shared__ __attribute__((aligned(16))) float sK[kC * kLD];   // phi(K), rotated
-    __shared__ __attribute__((aligned(16))) float sV[kC * kLD];   // V, rotated
-    __shared__ __attribute__((aligned(16))) float sZ[4][kC];      // dz, one partial per wavefront
-    const int64_t c = blockIdx.x, h = blockIdx.y;
-    const int64_t t0 = c * kC;
-    const int nvalid = (int)(p.T - t0 < kC ? p.T - t0 : kC);
-
-    // workspace of the state scan and the episode-index count words are
-    // prepared (all-ones bytes) here, so that the later kernels find them
-    // ready (stream order)
+// Bound by instruction issue and its fixed start and end (18 us at T = 32768,
+// 4 heads, also with every load served by the L2; its reads take 11 us at copy
+// speed and its MFMAs 7).
+__global__ __launch_bounds__(256, 4) void linattn_summary_kernel(LinSummaryArgs p) {
+    __shared__ __attribute__((aligned(16))) float sV[2][kTileF];
+    const int64_t seg = blockIdx.x, h = blockIdx.y;
+    const LinLane L;
+    // header and episode-index count words, prepared (all-ones bytes) for the
+    // later kernels (stream order)
     {
         const int64_t nblk = (int64_t)gridDim.x * gridDim.y;
         const int64_t gid = (int64_t)(blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
         const u32x4 ones = {kEmpty32, kEmpty32, kEmpty32, kEmpty32};
         for (int64_t i = gid; i < p.fill16; i += nblk * 256) p.fill[i] = ones;
     }
-
-    // K, V rows and the begin flags are all loaded at once; every wavefront
-    // finds the chunk's last begin step with one ballot (lane = row), and
-    // rows before it are then selected to zeros in both phi(K) and V (a
-    // select, so non-finite values there never enter)
-    f32x4 kreg[4], vreg[4];
-    fetch_rows(kreg, p.k, t0, p.H, h, 0, nvalid);
-    fetch_rows(vreg, p.v, t0, p.H, h, 0, nvalid);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const uint64_t bm = __ballot(lane < nvalid && is_begin(p.start, t0 + lane));
-    const int last = bm ? 63 - __builtin_clzll(bm) : -1;
-    const int lo = last > 0 ? last : 0;
-    // dz: each thread sums its four rows of phi(K) per column, then the four
-    // lanes of a wavefront that hold the same columns (lane ^ 16, lane ^ 32)
-    f32x4 zp = {0.0f, 0.0f, 0.0f, 0.0f};
+    const int64_t seg0 = seg * p.chunks * kChunk;
+    // V goes through LDS (every wavefront takes all of its columns), the
+    // wavefront's 16 columns of K straight to registers
+    Frag vreg, kreg;
+    uint32_t flag;
+    auto fetch = [&](int ch) {
+        const int64_t t0 = seg0 + (int64_t)ch * kChunk;
+        const bool have = ch < p.chunks;
+        flag = fetch_flag(p.start, have ? t0 : 0, have ? p.T : 0);
+        fetch_chunk(vreg, chunk_rows(p.v, t0, p.T, p.H, h, have), L);
+        const ChunkRows ck = chunk_rows(p.k, t0, p.T, p.H, h, have);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int f = threadIdx.x + 256 * u;
-        const int row = f >> 4, c4 = (f & 15) * 4;
-        const bool in = row >= lo && row < nvalid;
-        f32x4 kv = kreg[u], vv = vreg[u];
-        kv.x = in ? phi(kv.x) : 0.0f; kv.y = in ? phi(kv.y) : 0.0f;
-        kv.z = in ? phi(kv.z) : 0.0f; kv.w = in ? phi(kv.w) : 0.0f;
-        vv.x = in ? vv.x : 0.0f; vv.y = in ? vv.y : 0.0f; vv.z = in ? vv.z : 0.0f; vv.w = in ? vv.w : 0.0f;
-        *(f32x4*)(sK + row * kLD + rot_col(row, c4)) = kv;
-        *(f32x4*)(sV + row * kLD + rot_col(row, c4)) = vv;
-        zp.x += kv.x; zp.y += kv.y; zp.z += kv.z; zp.w += kv.w;
-    }
+        for (int b = 0; b < 4; ++b)
 #pragma unroll
-    for (int m = 16; m < 64; m <<= 1) {
-        zp.x += __shfl_xor(zp.x, m, 64); zp.y += __shfl_xor(zp.y, m, 64);
-        zp.z += __shfl_xor(zp.z, m, 64); zp.w += __shfl_xor(zp.w, m, 64);
-    }
-    if (lane < 16) *(f32x4*)(&sZ[w][lane * 4]) = zp;
-    __syncthreads();
-
-    f32x4 acc[4];
+            for (int q = 0; q < 4; ++q) kreg[b][q] = ck.load1(16 * b + 4 * L.g + q, 16 * L.w + L.c);
+    };
+    fetch(0);
+    Frag st;                                   // st[s][r] = dS[16 w + c][16 r + 4 g + s]
 #pragma unroll
-    for (int jt = 0; jt < 4; ++jt) acc[jt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    // C[n][kd] = sum_j V[j][n] phi(K)[j][kd] = dS^T: A = V^T, B = phi(K), both k-major
-    mfma_64x64x64<false, false>(sV, sK, acc);
-
-    float* out = p.dS + (c * p.H + h) * kStateWords;
+    for (int s = 0; s < 4; ++s) st[s] = zero4();
+    float z = 0.0f;                            // dz[16 w + c], this lane's rows
+    bool any = false;
+#pragma unroll 1
+    for (int ch = 0; ch < p.chunks; ++ch) {
+        float* const sv = sV[ch & 1];
+        stage_chunk<false>(sv, vreg, L);
+        Frag kc;
 #pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
+        for (int b = 0; b < 4; ++b) kc[b] = phi4(kreg[b]);
+        const uint64_t m = begin_bits(flag, seg0 + (int64_t)ch * kChunk, p.T);
+        any = any || m != 0;
+        barrier_lds();
+        fetch(ch + 1);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int n = 16 * w + 4 * (lane >> 4) + r;
-            const int kd = 16 * jt + (lane & 15);
-            out[n * kC + kd] = acc[jt][r];
+        for (int b = 0; b < 4; ++b) {
+            const uint32_t mb = block_bits(m, b);
+            Frag vc;
+            lds_cf(vc, sv, 16 * b, L);
+            if (mb) {
+                const uint32_t keep = bit_range(31 - __builtin_clz(mb), kBlk);
+                select_rows(vc, keep, L);
+                select_rows(kc[b], keep, L);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) st[s] = zero4();
+                z = 0.0f;
+            }
+            z += (kc[b].x + kc[b].y) + (kc[b].z + kc[b].w);
+            state_add(st, vc, kc[b]);
         }
     }
-    if (threadIdx.x < kC) {
-        const int t = threadIdx.x;
-        out[kC * kC + t] = (sZ[0][t] + sZ[1][t]) + (sZ[2][t] + sZ[3][t]);
+    float* const out = p.states + (seg * p.H + h) * kStateWords;
+    store_state_n(out, st, L);
+    z = sum_g(z);
+    if (L.g == 0) out[kDim * kDim + 16 * L.w + L.c] = z;
+    if (h == 0 && L.tid == 0) p.R[seg] = any ? 1 : 0;
+}
+
+// ---------------------------------------------------------------- state scan
+// Segmented prefix sum of the segment states, in place, from the first
+// segment on (REV: from the last back): y_s = x_s when segment s holds a begin
+// step, else x_s + y_{s-1} (REV: y_{s+1}).  A workgroup takes one 128-byte line
+// of the states (8 16-byte columns) and all segments, 32 RPT of them at a
+// time: thread (grp, col) holds RPT consecutive segments of a column in
+// registers, the 32 groups combine through LDS.  Loads go through a buffer
+// resource, so the edges need no branches and all of them are in flight at
+// once: the scan is one read and one write of the states (128 segments of 4
+// heads 6.3 us, 512 segments 12.8 us = 5.3 TB/s; predicated pointer loads took
+// 12 us on 256 segments against 8.6).
+constexpr int kScanCols = 8, kScanGroups = 32;
+template <int RPT, bool REV>
+__global__ __launch_bounds__(256) void state_scan_kernel(LinScanArgs p) {
+    __shared__ f32x4 s_tot[kScanGroups][kScanCols];
+    __shared__ uint32_t s_flag[kScanGroups];
+    constexpr int kTile = kScanGroups * RPT;
+    const int col = threadIdx.x % kScanCols, grp = threadIdx.x / kScanCols;
+    const uint32_t row_bytes = (uint32_t)(p.width * 4);
+    const uint32_t c0 = (uint32_t)(blockIdx.x * kScanCols + col) * 16u;   // width is a multiple of 32 floats
+    f32x4 carry = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int64_t base = 0; base < p.n; base += kTile) {
+        // the tile's segments in memory order: s0 .. s0 + rows - 1; place l of
+        // the scan order is segment l (REV: rows - 1 - l) among them
+        const int rows = (int)(p.n - base < kTile ? p.n - base : kTile);
+        const int64_t s0 = REV ? p.n - base - rows : base;
+        const Rsrc rs = make_rsrc(p.states + s0 * p.width, (int64_t)rows * row_bytes);
+        const Rsrc rr = make_rsrc(p.R + s0, rows);
+        f32x4 x[RPT];
+        uint32_t fl[RPT], off[RPT];
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const int l = grp * RPT + i;
+            const int s = REV ? rows - 1 - l : l;
+            off[i] = l < rows ? (uint32_t)s * row_bytes + c0 : kOob;
+            fl[i] = bload_u8(rr, l < rows ? (uint32_t)s : kOob);
+            x[i] = bload4(rs, off[i]);
+        }
+        uint32_t flag = 0;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) flag |= (fl[i] != 0u ? 1u : 0u) << i;
+        f32x4 tot = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int i = 0; i < RPT; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tot[e] = (flag >> i) & 1u ? x[i][e] : tot[e] + x[i][e];
+        __syncthreads();                               // the last round's totals have been read
+        s_tot[grp][col] = tot;
+        if (col == 0) s_flag[grp] = flag != 0u;
+        __syncthreads();
+        f32x4 y = carry;
+#pragma unroll 8
+        for (int k = 0; k < kScanGroups; ++k) {
+            const f32x4 t = s_tot[k][col];
+            const bool f = s_flag[k] != 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                carry[e] = f ? t[e] : carry[e] + t[e];
+                y[e] = k + 1 == grp ? carry[e] : y[e];    // the state before this thread's run
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = (flag >> i) & 1u ? x[i][e] : y[e] + x[i][e];
+            const u32x4 w = {__float_as_uint(y.x), __float_as_uint(y.y), __float_as_uint(y.z), __float_as_uint(y.w)};
+            __builtin_amdgcn_raw_buffer_store_b128(w, rs, (int)off[i], 0, 0);
+        }
     }
-    if (h == 0 && threadIdx.x == 0) p.R[c] = last >= 0 ? 1 : 0;
 }
 
 // ------------------------------------------------------------------- output
 
-__global__ __launch_bounds__(256, 4) void linattn_output_kernel(LinOutputArgs p) {
-    // two LDS tiles, reused in turn: (phi(Q), phi(K)) -> (phi(Q), S_in^T) ->
-    // (masked A, V rotated); 35 KB per workgroup, four workgroups per CU
-    __shared__ __attribute__((aligned(16))) float X0[kC * kLD];
-    __shared__ __attribute__((aligned(16))) float X1[kC * kLD];
-    __shared__ float sZ[kC];
+// Three workgroups' registers per CU; at T = 32768 and 4 heads the grid has two
+// per CU, MFMAs keep the matrix cores 47 % busy (41 us against 17 us of MFMA
+// and 25 us of traffic), the rest being the phases of a chunk (staging, A of
+// the own block, z and den) that two wavefronts per SIMD only partly overlap.
+// Loading V a phase earlier (43 us) or a branch-free path for chunks without
+// begin steps (41 us) gained nothing.
+__global__ __launch_bounds__(256, 3) void linattn_output_kernel(LinOutputArgs p) {
+    __shared__ __attribute__((aligned(16))) float sQ[kTileF];     // phi(Q)
+    __shared__ __attribute__((aligned(16))) float sK[kTileF];     // phi(K)
+    __shared__ f32x4 sA[4][64];                                   // each block's masked A, as mul_rows returns it
+    __shared__ __attribute__((aligned(16))) float sZ[5][kDim];    // column sums of each block; [4]: z before the chunk
+    __shared__ float sDen[kChunk];                                // 1 / den of the chunk's rows
+    const int64_t seg = blockIdx.x, h = blockIdx.y;
+    const LinLane L;
+    const int64_t seg0 = seg * p.chunks * kChunk;
+    const int64_t left = (p.T - seg0 + kChunk - 1) / kChunk;
+    const int nch = (int)(left < p.chunks ? left : p.chunks);
 
-    const int64_t c = blockIdx.x, h = blockIdx.y;
-    const int64_t t0 = c * kC;
-    const int nvalid = (int)(p.T - t0 < kC ? p.T - t0 : kC);
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    // the causal products give the wavefront of row block rb (rb + 1) / 4 of
-    // a full product's work, and wavefront w of a workgroup usually runs on
-    // SIMD w: row blocks rotate with the chunk so that the SIMDs of a CU
-    // share the triangle evenly across its workgroups
-    const int rb = (w + (int)blockIdx.x) & 3;
-
-    // row `lane` of the chunk: begin flag, and the last begin at or before it
-    // (an inclusive max-scan across the wavefront; every wavefront has all 64)
-    const bool beg = lane < nvalid && is_begin(p.start, t0 + lane);
-    int rmax = beg ? lane : -1;
+    Frag qreg, kreg, vreg;                     // next chunk; vreg[b]: slices of V
+    uint32_t flag;
+    auto fetch_qk = [&](int ch) {
+        const int64_t t0 = seg0 + (int64_t)ch * kChunk;
+        const bool have = ch < nch;
+        flag = fetch_flag(p.start, have ? t0 : 0, have ? p.T : 0);
+        fetch_chunk(kreg, chunk_rows(p.k, t0, p.T, p.H, h, have), L);
+        fetch_chunk(qreg, chunk_rows(p.q, t0, p.T, p.H, h, have), L);
+    };
+    auto fetch_v = [&](int ch) {
+        const int64_t t0 = seg0 + (int64_t)ch * kChunk;
+        const ChunkRows cv = chunk_rows(p.v, t0, p.T, p.H, h, ch < nch);
 #pragma unroll
-    for (int k = 1; k < 64; k <<= 1) {
-        const int o = __shfl_up(rmax, k, 64);
-        if (lane >= k) rmax = rmax > o ? rmax : o;
-    }
-
-    // every global load of the workgroup is issued before any LDS store: q,
-    // k, v and S_in into registers (S and V wait there for their turn in LDS)
-    f32x4 qreg[4], kreg[4], vreg[4], sreg[4];
-    fetch_rows(qreg, p.q, t0, p.H, h, 0, nvalid);
-    fetch_rows(kreg, p.k, t0, p.H, h, 0, nvalid);
-    const int bad = fetch_rows(vreg, p.v, t0, p.H, h, 0, nvalid);
-    // S_in: the state after the previous chunk (an empty range, read as
-    // zeros, for the first chunk)
-    const Rsrc rs_s = make_rsrc(p.Sinc + (c > 0 ? ((c - 1) * p.H + h) * kStateWords : 0),
-                                c > 0 ? kStateWords * 4 : 0);
+        for (int b = 0; b < 4; ++b)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int f = tid + 256 * u;
-        const u32x4 wv = __builtin_amdgcn_raw_buffer_load_b128(rs_s, ((f >> 4) * kC + (f & 15) * 4) * 4, 0, 0);
-        sreg[u] = f32x4{__uint_as_float(wv.x), __uint_as_float(wv.y), __uint_as_float(wv.z), __uint_as_float(wv.w)};
-    }
-    const float zin = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_s, (kC * kC + (tid & (kC - 1))) * 4, 0, 0));
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int f = tid + 256 * u;
-        const int row = f >> 4, c4 = (f & 15) * 4;
-        // phi of every row: rows past T read zeros (phi = 1), and their
-        // entries are masked out of A or belong to outputs never stored
-        f32x4 qv = qreg[u], kv = kreg[u];
-        qv.x = phi(qv.x); qv.y = phi(qv.y); qv.z = phi(qv.z); qv.w = phi(qv.w);
-        kv.x = phi(kv.x); kv.y = phi(kv.y); kv.z = phi(kv.z); kv.w = phi(kv.w);
-        *(f32x4*)(X0 + row * kLD + c4) = qv;
-        *(f32x4*)(X1 + row * kLD + c4) = kv;
-    }
-    if (tid < kC) sZ[tid] = zin;
-    const bool nonfinite_v = __syncthreads_or(bad) != 0;
+            for (int q = 0; q < 4; ++q) vreg[b][q] = cv.load1(16 * b + 4 * L.g + q, 16 * L.w + L.c);
+    };
+    fetch_qk(0);
+    Frag st;                                   // st[s][r] = S[16 r + 4 g + s][16 w + c]
+    const Rsrc rs_s = state_rows(p.states, seg - 1, p.H, h, seg > 0);
+    load_state_kd(st, rs_s, L);
+    const float z_in = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_s, (kDim * kDim + L.lane) * 4, 0, 0));
+    fetch_v(0);
+    if (L.w == 0) sZ[4][L.lane] = z_in;
 
-    // episode index of the chunk's steps (head-0 workgroups): wavefront 2
-    // publishes the chunk's own begin count at once, wavefront 1 looks back
-    // for the count before the chunk, publishes the running count and writes
-    // the indices (publishing and polling use different wavefronts)
-    if (p.idx != nullptr && h == 0 && (w == 1 || w == 2)) {
-        const uint64_t m = __ballot(beg);
-        const uint32_t c_chunk = (uint32_t)__builtin_popcountll(m);
-        if (w == 2) {
-            if (lane == 0) publish64(p.cnt + c, (c == 0 ? kCountIncl : kCountOwn) | c_chunk);
-        } else {
-            const uint32_t before = c == 0 ? 0u : count_lookback(p.cnt, c - 1, 1, p.timeout);
-            if (lane == 0 && c > 0) publish64(p.cnt + c, kCountIncl | (before + c_chunk));
-            const uint32_t upto = (uint32_t)__builtin_popcountll(m & ((2ull << lane) - 1ull));
-            if (lane < nvalid) p.idx[t0 + lane] = (int32_t)(before + upto) - 1;
+    // episode index (head-0 workgroups): wavefront 2 publishes the segment's
+    // own begin count at once; wavefront 1 looks up the count before it when
+    // the outputs are done
+    const bool want_idx = p.idx != nullptr && h == 0;
+    if (want_idx && L.w == 2) {
+        uint32_t own = 0;
+        for (int ch = 0; ch < nch; ++ch) {
+            const int64_t t0 = seg0 + (int64_t)ch * kChunk;
+            const int64_t t = t0 + L.lane;
+            own += (uint32_t)__builtin_popcountll(
+                __ballot(t < p.T && (t == 0 || fetch_flag(p.start, t0, p.T) != 0u)));
         }
+        if (L.lane == 0) publish64(p.cnt + seg, (seg == 0 ? kCountIncl : kCountOwn) | own);
     }
 
-    f32x4 accA[4], accS[4];
+#pragma unroll 1
+    for (int ch = 0; ch < nch; ++ch) {
+        const int64_t t0 = seg0 + (int64_t)ch * kChunk;
+        const uint64_t m = begin_bits(flag, t0, p.T);
+        stage_chunk<true>(sK, kreg, L);
+        stage_chunk<true>(sQ, qreg, L);
+        Frag vs;
 #pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
-        accA[jt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        accS[jt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-    // A[i][j] = phi(q_i) . phi(k_j); column tiles above the diagonal are
-    // masked out entirely and skipped
-    mfma_64x64x64<true, true>(X0, X1, accA, rb, rb);
-    __syncthreads();                            // every wavefront is done with phi(K)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int f = tid + 256 * u;
-        *(f32x4*)(X1 + (f >> 4) * kLD + (f & 15) * 4) = sreg[u];
-    }
-    __syncthreads();
-    // QS[i][n] = sum_kd phi(q_i)[kd] S_in[kd][n], needed only by rows before
-    // the chunk's first begin (their episode started in an earlier chunk)
-    const uint64_t bmask = __ballot(beg);
-    const int fbeg = bmask ? __builtin_ctzll(bmask) : kC;
-    if (16 * rb < fbeg) mfma_64x64x64<true, true>(X0, X1, accS, 3, rb);
+        for (int b = 0; b < 4; ++b) vs[b] = vreg[b];
+        barrier_lds();
+        fetch_qk(ch + 1);
 
-    // mask A to each row's episode (a select: excluded entries are exact
-    // zeros), then the row sums and phi(q_i).z_in, reduced across lanes
-    int ri[4];
-    float den[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = 16 * rb + 4 * (lane >> 4) + r;
-        ri[r] = __shfl(rmax, i, 64);
-        float rs = 0.0f;
-#pragma unroll
-        for (int jt = 0; jt < 4; ++jt) {
-            const int j = 16 * jt + (lane & 15);
-            const bool keep = i < nvalid && j <= i && j >= (ri[r] > 0 ? ri[r] : 0);
-            accA[jt][r] = keep ? accA[jt][r] : 0.0f;
-            rs += accA[jt][r];
-        }
-        const int kd = 4 * (lane & 15);
-        const f32x4 qv = *(const f32x4*)(X0 + i * kLD + kd);
-        float qz = qv.x * sZ[kd] + qv.y * sZ[kd + 1] + qv.z * sZ[kd + 2] + qv.w * sZ[kd + 3];
-        rs = sum16(rs);
-        qz = sum16(qz);
-        den[r] = rs + (ri[r] < 0 ? qz : 0.0f);
-    }
-    __syncthreads();                            // every wavefront is done with phi(Q) and S
-    float* const sA = X0;
-    float* const sV = X1;
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sA[(16 * rb + 4 * (lane >> 4) + r) * kLD + 16 * jt + (lane & 15)] = accA[jt][r];
-    }
-    store_rows<true>(sV, vreg);
-    __syncthreads();
-
-    f32x4 accO[4];
-#pragma unroll
-    for (int jt = 0; jt < 4; ++jt) accO[jt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    if (!nonfinite_v) {
-        mfma_64x64x64_tril(sA, sV, accO, rb);       // num[i][n] = sum_{j <= i} A[i][j] V[j][n]
-    } else {
-        // A non-finite value in V would reach other episodes of this chunk
-        // through the dense product (0 * NaN = NaN); sum each row's own
-        // episode explicitly instead.
-#pragma unroll
-        for (int jt = 0; jt < 4; ++jt) {
+        // ---- block w alone: A and its row sums, the block's column sums of
+        // phi(K) from its last begin on
+        const uint32_t mw = block_bits(m, L.w);
+        const int first = first_of(mw, L.c);
+        const bool cont = (mw & ((2u << L.c) - 1u)) == 0u;       // row c's episode began before the block
+        Frag qr;
+        float den = 0.0f;
+        {
+            Frag kr;
+            lds_rf(kr, sK, 16 * L.w, L);
+            lds_rf(qr, sQ, 16 * L.w, L);
+            f32x4 at = mul_rows(kr, qr);                          // phi(k_j) . phi(q_c), j = 4 g + r
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int i = 16 * rb + 4 * (lane >> 4) + r;
-                const int n = 16 * jt + (lane & 15);
-                float s = 0.0f;
-                for (int j = (ri[r] > 0 ? ri[r] : 0); j <= i && j < nvalid; ++j)
-                    s += sA[i * kLD + j] * sV[j * kLD + rot_col(j, n)];
-                accO[jt][r] = s;
+                const int j = 4 * L.g + r;
+                at[r] = j <= L.c && j >= first ? at[r] : 0.0f;
+                den += at[r];
             }
+            sA[L.w][L.lane] = at;
+            Frag kc;
+            lds_cf(kc, sK, 16 * L.w, L);
+            if (mw) select_rows(kc, bit_range(31 - __builtin_clz(mw), kBlk), L);
+            const f32x4 zs = col_sums(kc, f32x4{1.0f, 1.0f, 1.0f, 1.0f});
+            if (L.g == 0) *(f32x4*)(&sZ[L.w][L.cm]) = zs;
+        }
+        barrier_lds();
+        float qz = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            f32x4 z = *(const f32x4*)(&sZ[4][16 * r + 4 * L.g]);
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+                if (b < L.w) z = z_then(z, block_bits(m, b), *(const f32x4*)(&sZ[b][16 * r + 4 * L.g]));
+#pragma unroll
+            for (int s = 0; s < 4; ++s) qz = __builtin_fmaf(qr[r][s], z[s], qz);
+        }
+        den = sum_g(den + (cont ? qz : 0.0f));
+        // one reciprocal per row (correctly rounded) and a product per output
+        if (L.g == 0) sDen[16 * L.w + L.c] = 1.0f / den;
+
+        // ---- the four blocks in order against the wavefront's 16 columns
+        f32x4 o[4];
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const uint32_t mb = block_bits(m, b);
+            Frag kc;
+            lds_rf(qr, sQ, 16 * b, L);
+            lds_cf(kc, sK, 16 * b, L);
+            o[b] = mul_state(st, qr);
+            if (mb) o[b] = select4((mb & ((2u << L.c) - 1u)) == 0u, o[b]);
+            o[b] = mul_slice_kept(vs[b], sA[b][L.lane], bit_range(first_of(mb, L.c), L.c + 1), o[b], L);
+            if (mb) {
+                const uint32_t keep = bit_range(31 - __builtin_clz(mb), kBlk);
+                select_rows(kc, keep, L);
+                select_rows(vs[b], keep, L);
+#pragma unroll
+                for (int s = 0; s < 4; ++s) st[s] = zero4();
+            }
+            state_add(st, kc, vs[b]);
+        }
+        fetch_v(ch + 1);
+        barrier_lds();
+        const ChunkRows co = chunk_rows(p.out, t0, p.T, p.H, h);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) co.store_nt(16 * b + L.c, 16 * L.w + 4 * L.g, o[b] * sDen[16 * b + L.c]);
+        if (L.w == 3) {                                           // z before the next chunk
+            float z = sZ[4][L.lane];
+#pragma unroll
+            for (int b = 0; b < 4; ++b) z = block_bits(m, b) ? sZ[b][L.lane] : z + sZ[b][L.lane];
+            sZ[4][L.lane] = z;
         }
     }
 
-    // one reciprocal per row (correctly rounded) and a product per output
-    float rden[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) rden[r] = 1.0f / den[r];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int i = 16 * rb + 4 * (lane >> 4) + r;
-        if (i < nvalid) {
-            float* orow = p.out + ((t0 + i) * p.H + h) * kC + (lane & 15);
-#pragma unroll
-            for (int jt = 0; jt < 4; ++jt) {
-                const float num = accO[jt][r] + (ri[r] < 0 ? accS[jt][r] : 0.0f);
-                __builtin_nontemporal_store(num * rden[r], &orow[16 * jt]);   // written once, read by no later kernel
-            }
+    if (want_idx && L.w == 1) {
+        uint32_t count = seg == 0 ? 0u : count_lookback(p.cnt, seg - 1, 1, p.timeout);
+        for (int ch = 0; ch < nch; ++ch) {
+            const int64_t t0 = seg0 + (int64_t)ch * kChunk;
+            const int64_t t = t0 + L.lane;
+            const uint64_t mk = __ballot(t < p.T && (t == 0 || fetch_flag(p.start, t0, p.T) != 0u));
+            if (t < p.T) p.idx[t] = (int32_t)(count + __builtin_popcountll(mk & ((2ull << L.lane) - 1ull))) - 1;
+            count += (uint32_t)__builtin_popcountll(mk);
         }
+        if (L.lane == 0 && seg > 0) publish64(p.cnt + seg, kCountIncl | count);
     }
 }
 
 // ------------------------------------------------------------------ launch
 
-hipError_t linattn_summary_launch(const LinSummaryArgs& a, hipStream_t s) {
-    const int64_t nch = (a.T + kC - 1) / kC;
-    hipLaunchKernelGGL(linattn_summary_kernel, dim3((unsigned)nch, (unsigned)a.H), dim3(256), 0, s, a);
+hipError_t linattn_summary_launch(const LinSummaryArgs& a, int64_t nseg, hipStream_t s) {
+    hipLaunchKernelGGL(linattn_summary_kernel, dim3((unsigned)nseg, (unsigned)a.H), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t linattn_output_launch(const LinOutputArgs& a, hipStream_t s) {
-    const int64_t nch = (a.T + kC - 1) / kC;
-    hipLaunchKernelGGL(linattn_output_kernel, dim3((unsigned)nch, (unsigned)a.H), dim3(256), 0, s, a);
+template <bool REV>
+static void scan_launch(const LinScanArgs& a, hipStream_t s) {
+    const dim3 grid((unsigned)(a.width / (4 * kScanCols))), block(256);
+    // the fewest rows per thread that take all segments at once
+    if (a.n <= 2 * kScanGroups) hipLaunchKernelGGL((state_scan_kernel<2, REV>), grid, block, 0, s, a);
+    else if (a.n <= 4 * kScanGroups) hipLaunchKernelGGL((state_scan_kernel<4, REV>), grid, block, 0, s, a);
+    else if (a.n <= 8 * kScanGroups) hipLaunchKernelGGL((state_scan_kernel<8, REV>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((state_scan_kernel<16, REV>), grid, block, 0, s, a);
+}
+
+hipError_t linattn_scan_launch(bool rev, const LinScanArgs& a, hipStream_t s) {
+    if (rev) scan_launch<true>(a, s);
+    else scan_launch<false>(a, s);
+    return hipGetLastError();
+}
+
+hipError_t linattn_output_launch(const LinOutputArgs& a, int64_t nseg, hipStream_t s) {
+    hipLaunchKernelGGL(linattn_output_kernel, dim3((unsigned)nseg, (unsigned)a.H), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -105,7 +105,7 @@ def source_hash(root):
 # kernels each timed library call launches (name after "memoroid::"), per
 # workload, once per call
 _DIAG = {"fwd": ["diag_fwd_kernel"], "bwd": ["diag_bwd_kernel"]}
-_LIN_FWD = ["linattn_summary_kernel", "diag_fwd_kernel", "linattn_output_kernel"]
+_LIN_FWD = ["linattn_summary_kernel", "state_scan_kernel", "linattn_output_kernel"]
 CALLS = {
     2: _DIAG,
     4: {"fwd": ["diag_fwd_kernel"]},
@@ -116,8 +116,8 @@ CALLS = {
         "sample": ["tbb_rows_kernel", "tbb_gather_kernel"]},
     3: {"linattn_fwd": _LIN_FWD},
     9: {"linattn_fwd": _LIN_FWD,
-        "linattn_bwd": ["linattn_summary_kernel", "diag_fwd_kernel", "linattn_bwd_summary_kernel", "diag_bwd_kernel",
-                        "linattn_bwd_grad_kernel"]},
+        "linattn_bwd": ["linattn_summary_kernel", "state_scan_kernel", "linattn_dq_kernel", "state_scan_kernel",
+                        "linattn_dkv_kernel"]},
 }
 
 
