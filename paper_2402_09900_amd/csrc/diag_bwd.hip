@@ -23,10 +23,14 @@
 
 namespace memoroid {
 
-template <Kind K, int VEC, int R, bool AINV, bool FFM = false>
+// QP: the plan's lane-group width when it is fixed at compile time (8, a whole
+// chain row of vector-wide lanes), 0 when it comes from the plan, as in the
+// forward scan.
+template <Kind K, int VEC, int R, bool AINV, int QP, bool FFM = false>
 __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
     static_assert(!FFM || (K == K_C64 && AINV), "FFM: complex state, generated a");
-    static_assert(R >= 1 && R <= 32, "a lane's steps are bits of 32-bit masks");
+    static_assert(R >= 1 && R < 32, "a lane's steps (and the one after) are bits of 32-bit masks");
+    static_assert(QP == 0 || QP == 8, "fixed group width: whole chain rows");
     using S = typename StateOf<K>::type;
     using C = Codec<K, VEC>;
     using SegT = Seg<S, VEC>;
@@ -73,7 +77,7 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
     const int64_t tile = p.nt - 1 - k;              // tiles run from the tape end
     const int b = chain / p.nfb;
     const int fb = chain - b * p.nfb;
-    const int Qp = p.Qp;
+    const int Qp = QP ? QP : p.Qp;
     const int qsh = __builtin_ctz((unsigned)Qp);   // Qp is a power of two
     const int Gw = 64 >> qsh;
     const int wave = tid >> 6;
@@ -122,11 +126,17 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
     // loads, so that the table need not wait for them
     FfmParam fpar{0.f, 0.f};
     if constexpr (FFM) fpar = ffm_param_load(p.alpha, p.omega, p.d, p.ffm_c, (int64_t)fb * Dp, Dp);
-    uint32_t fl[R + 1];
-#pragma unroll
-    for (int r = 0; r <= R; ++r) fl[r] = bload_u8(rs_st, lrow + r);
     const int64_t t_last = (tile_row0 + L < T ? tile_row0 + L : T) - 1;
-    const uint32_t fl_after = bload_u8(rs_st, (uint32_t)(t_last + 1 - tile_row0));
+    constexpr bool kBits = QP >= 8;
+    StepFlags<R, 1> sf;
+    uint32_t fl[kBits ? 1 : R + 1], fl_after = 0;
+    if constexpr (kBits) {
+        sf.load(rs_st, (uint32_t)(wave * Gw * R));
+    } else {
+#pragma unroll
+        for (int r = 0; r <= R; ++r) fl[r] = bload_u8(rs_st, lrow + r);
+        fl_after = bload_u8(rs_st, (uint32_t)(t_last + 1 - tile_row0));
+    }
     __builtin_amdgcn_sched_barrier(0);
     RawVec<K, VEC> rg[R];
     RawVec<K, VEC> ra[AINV ? 1 : R];
@@ -140,13 +150,29 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
     }
     __builtin_amdgcn_sched_barrier(0);
     uint32_t ends = 0, begins = 0, valid = 0;
+    if constexpr (kBits) {
+        // flags past T read zero; the step after the wavefront's last is the
+        // bit string's last
+        uint64_t w[StepFlags<R, 1>::W];
+        sf.words(w);
+        if (tile == 0 && wave == 0) w[0] |= 1ull;
+        constexpr int kAfter = 8 * R;                          // Gw * R
+        fl_after = (uint32_t)(w[kAfter / 64] >> (kAfter % 64)) & 1u;   // the last wavefront's: the step after the tile
+        const uint32_t both = bits_at<R + 1>(w, j * R);
+        const int left = (int)(rows_left <= L ? rows_left : L + 1) - (int)lrow;   // steps to T, or past the tile
+        valid = left >= R ? (1u << R) - 1u : left <= 0 ? 0u : (1u << left) - 1u;
+        begins = both & valid;
+        ends = (both >> 1) & valid;
+        if (left >= 1 && left <= R) ends |= 1u << (left - 1);  // the tape's last step
+    } else {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t t = row0 + r;
-        const uint32_t in = t < T ? 1u : 0u;
-        valid |= in << r;
-        begins |= (in & ((t == 0 ? 1u : 0u) | (fl[r] != 0u ? 1u : 0u))) << r;
-        ends |= (in & ((t + 1 == T ? 1u : 0u) | (fl[r + 1] != 0u ? 1u : 0u))) << r;
+        for (int r = 0; r < R; ++r) {
+            const int64_t t = row0 + r;
+            const uint32_t in = t < T ? 1u : 0u;
+            valid |= in << r;
+            begins |= (in & ((t == 0 ? 1u : 0u) | (fl[r] != 0u ? 1u : 0u))) << r;
+            ends |= (in & ((t + 1 == T ? 1u : 0u) | (fl[r + 1] != 0u ? 1u : 0u))) << r;
+        }
     }
     S ainv[VEC];
     if constexpr (FFM) {
@@ -184,45 +210,39 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
     // D1 = sum_t l_t conj(h_{t-1}) and D2 = sum_t c_t conj(h_{t-1}) (da's
     // partial is D1 + lam_in D2), and for FFM sum_v Re(l_t) per step (the
     // input gradient adds Re over the lane's features, which share one row j).
+    // With an invariant coefficient c_t is its power R - r above the lane's
+    // last end, so D2 is a Horner sum over ascending steps that an end restarts,
+    // and neither it nor the segment's A needs a product per step of its own.
     constexpr bool kFoldDa = AINV && std::is_same<S, cf>::value;
     constexpr int RF = FFM ? R : 1;
     float lre[RF];
-    S d1[VEC], d2[VEC], cp[VEC];
-    bool alive = true, d2_live = false;      // c_t not forced to zero yet / some term of D2 counts
+    S d1[VEC], d2[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
         d1[v] = s_zero<S>();
         d2[v] = s_zero<S>();
-        cp[v] = s_one<S>();
     }
+    // no da at a begin step, nor past T (selects: the step T reads h_{T-1},
+    // and 0 * Inf would reach the sum)
+    const uint32_t no_da_bits = begins | ~valid;
     SegT own = seg_identity<S, VEC>();
 #pragma unroll
     for (int r = R - 1; r >= 0; --r) {
         const bool e = (ends >> r) & 1u;
-        // no da at a begin step, nor past T (a select: the step T reads
-        // h_{T-1}, and 0 * Inf would reach the sum)
-        const bool no_da = ((begins | ~valid) >> r) & 1u;
+        const bool no_da = (no_da_bits >> r) & 1u;
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
             const S gv = C::get(rg[r], v);
             const S cv = coef(r, v);
             const S nh = mad(cv, own.H[v], gv);
-            const S na = own.A[v] * cv;
             own.H[v] = e ? gv : nh;
-            own.A[v] = e ? s_one<S>() : na;
-            if constexpr (kFoldDa) {
-                const S ncp = cv * cp[v];
-                cp[v] = e ? s_zero<S>() : ncp;
-                if (want_da) {
-                    const S hc = conj(C::get(rh[r], v));
-                    d1[v] = no_da ? d1[v] : mad(own.H[v], hc, d1[v]);
-                    d2[v] = no_da ? d2[v] : mad(cp[v], hc, d2[v]);
-                }
+            if constexpr (!AINV) {
+                const S na = own.A[v] * cv;
+                own.A[v] = e ? s_one<S>() : na;
             }
-        }
-        if constexpr (kFoldDa) {
-            alive = alive && !e;
-            d2_live = d2_live || (alive && !no_da);
+            if constexpr (kFoldDa) {
+                if (want_da) d1[v] = no_da ? d1[v] : mad(own.H[v], conj(C::get(rh[r], v)), d1[v]);
+            }
         }
         if constexpr (FFM) {
             float sre = 0.0f;
@@ -232,11 +252,38 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
         }
     }
     own.f = ends != 0;
+    bool d2_live = false;                    // some term of D2 counts
+    if constexpr (kFoldDa) {
+        if (want_da) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const bool e = (ends >> r) & 1u;
+                const bool no_da = (no_da_bits >> r) & 1u;
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    const S hc = conj(C::get(rh[r], v));
+                    const S t = no_da ? d2[v] : d2[v] + hc;
+                    const S nd = ainv[v] * t;
+                    d2[v] = e ? s_zero<S>() : nd;
+                }
+            }
+            const uint32_t above = ends ? ~((2u << (31 - __builtin_clz(ends))) - 1u) : ~0u;
+            d2_live = (above & ~no_da_bits & ((1u << R) - 1u)) != 0u;
+        }
+    }
 
     // ---- scan the wavefront's groups (later groups first), then combine the
     // wavefront totals (later wavefronts first) through LDS
     SegT inc = own, exc;
-    wave_group_scan<S, VEC, true, kQpMax>(inc, exc, Qp);
+    if constexpr (AINV) {
+        // the factor of a lane's R steps is a^R (unused when it holds an end)
+        typename WideOf<S>::type aR[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) aR[v] = power<R>(widen(ainv[v]));
+        wave_group_scan_inv<S, VEC, true, kQpMax>(inc, exc, Qp, aR);
+    } else {
+        wave_group_scan<S, VEC, true, kQpMax>(inc, exc, Qp);
+    }
     if (j == 0) {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
@@ -328,14 +375,13 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
             // rows go to the chain-major workspace [chain][T][jpc], so that a
             // tile writes whole lines (ffm_bwd_finish_kernel puts them in
             // [B][T][m] order).
-            const int64_t cc = p.ffm_c;
-            const int csh = __builtin_ctzll((uint64_t)cc);
-            const int64_t jpc = Dp >> csh;
-            const int gsz = (int)(cc / VEC);
-            float* const dxw = p.dxr + (int64_t)chain * T * jpc;
+            const int csh = __builtin_ctz((unsigned)p.ffm_c);
+            const int jpc = Dp >> csh;
+            const int gsz = (int)p.ffm_c / VEC;
+            const Rsrc rs_w = make_rsrc(p.dxr + ((int64_t)chain * T + tile_row0) * jpc, rows_left * jpc * 4);
+            const uint32_t at = (q & (gsz - 1)) == 0 ? (lrow * jpc + ((q * VEC) >> csh)) * 4u : kOob;
 #pragma unroll
             for (int r = R - 1; r >= 0; --r) {
-                const int64_t t = row0 + r;
                 const bool e = (ends >> r) & 1u;
                 float part = lre[r];
 #pragma unroll
@@ -345,7 +391,7 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
                     part += re_part(lam[v]);
                 }
                 for (int off = 1; off < gsz; off <<= 1) part += lanes_xor(part, off);
-                if (t < T && (q & (gsz - 1)) == 0) dxw[t * jpc + ((q * VEC) >> csh)] = part;
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(part), rs_w, (int)(at + (uint32_t)(r * jpc) * 4u), 0, 0);
             }
         } else {
 #pragma unroll
@@ -496,23 +542,23 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float* in, float* out
 
 // ------------------------------------------------------------------ launch
 
-template <Kind K, int VEC, int R>
-static hipError_t launch_bwd(const DiagBwdArgs& args, int64_t ntiles, bool ainv, hipStream_t s) {
-    if (ainv)
-        hipLaunchKernelGGL((diag_bwd_kernel<K, VEC, R, true>), dim3((unsigned)ntiles), dim3(256), 0, s, args);
-    else
-        hipLaunchKernelGGL((diag_bwd_kernel<K, VEC, R, false>), dim3((unsigned)ntiles), dim3(256), 0, s, args);
+template <Kind K, int VEC, int R, bool AINV, bool FFM = false>
+static hipError_t launch_bwd(const DiagBwdArgs& args, int64_t ntiles, hipStream_t s) {
+    const dim3 grid((unsigned)ntiles), block(256);
+    if constexpr (VEC > 1) {
+        if (args.Qp == 8) {
+            hipLaunchKernelGGL((diag_bwd_kernel<K, VEC, R, AINV, 8, FFM>), grid, block, 0, s, args);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((diag_bwd_kernel<K, VEC, R, AINV, 0, FFM>), grid, block, 0, s, args);
     return hipGetLastError();
 }
 
 hipError_t ffm_bwd_launch(bool vec, const DiagBwdArgs& args, int64_t ntiles, hipStream_t s) {
     constexpr int RI = kFfmBwdRows;
-    if (vec)
-        hipLaunchKernelGGL((diag_bwd_kernel<K_C64, KindInfo<K_C64>::vec, RI, true, true>), dim3((unsigned)ntiles),
-                           dim3(256), 0, s, args);
-    else
-        hipLaunchKernelGGL((diag_bwd_kernel<K_C64, 1, RI, true, true>), dim3((unsigned)ntiles), dim3(256), 0, s, args);
-    return hipGetLastError();
+    return vec ? launch_bwd<K_C64, KindInfo<K_C64>::vec, RI, true, true>(args, ntiles, s)
+               : launch_bwd<K_C64, 1, RI, true, true>(args, ntiles, s);
 }
 
 // One workgroup: thread j < m forms dalpha[j], thread k < c forms domega[k]
@@ -679,13 +725,17 @@ hipError_t ffm_bwd_finish_launch(const FfmFinishArgs& a, hipStream_t s) {
 hipError_t diag_bwd_launch(int kind, bool vec, bool ainv, const DiagBwdArgs& args, int64_t ntiles,
                            hipStream_t s) {
     constexpr int RI = diag_rows(true, true), RS = diag_rows(true, false);
+    constexpr int VF = KindInfo<K_F32>::vec, VC = KindInfo<K_C64>::vec;
     if (kind == K_F32) {
-        if (ainv) return vec ? launch_bwd<K_F32, KindInfo<K_F32>::vec, RI>(args, ntiles, true, s) : launch_bwd<K_F32, 1, RI>(args, ntiles, true, s);
-        return vec ? launch_bwd<K_F32, KindInfo<K_F32>::vec, RS>(args, ntiles, false, s) : launch_bwd<K_F32, 1, RS>(args, ntiles, false, s);
+        if (ainv)
+            return vec ? launch_bwd<K_F32, VF, RI, true>(args, ntiles, s) : launch_bwd<K_F32, 1, RI, true>(args, ntiles, s);
+        return vec ? launch_bwd<K_F32, VF, RS, false>(args, ntiles, s) : launch_bwd<K_F32, 1, RS, false>(args, ntiles, s);
     }
     if (kind == K_C64) {
-        if (ainv) return vec ? launch_bwd<K_C64, KindInfo<K_C64>::vec, kBwdRowsC64Inv>(args, ntiles, true, s) : launch_bwd<K_C64, 1, RI>(args, ntiles, true, s);
-        return vec ? launch_bwd<K_C64, KindInfo<K_C64>::vec, RS>(args, ntiles, false, s) : launch_bwd<K_C64, 1, RS>(args, ntiles, false, s);
+        if (ainv)
+            return vec ? launch_bwd<K_C64, VC, kBwdRowsC64Inv, true>(args, ntiles, s)
+                       : launch_bwd<K_C64, 1, RI, true>(args, ntiles, s);
+        return vec ? launch_bwd<K_C64, VC, RS, false>(args, ntiles, s) : launch_bwd<K_C64, 1, RS, false>(args, ntiles, s);
     }
     return hipErrorInvalidValue;
 }

@@ -51,10 +51,14 @@
 
 namespace memoroid {
 
-template <Kind IN, Kind OUT, int VEC, int R, bool AINV, bool FFM = false>
+// QP: the plan's lane-group width when it is fixed at compile time (8, a whole
+// chain row of vector-wide lanes: every vectorised call with at least one line
+// of features), 0 when it comes from the plan.
+template <Kind IN, Kind OUT, int VEC, int R, bool AINV, int QP, bool FFM = false>
 __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
     static_assert(!FFM || (IN == K_C64 && OUT == K_C64 && AINV), "FFM: complex state, generated a");
     static_assert(R >= 1 && R <= 32, "a lane's steps are bits of 32-bit masks");
+    static_assert(QP == 0 || QP == 8, "fixed group width: whole chain rows");
     using S = typename StateOf<IN>::type;
     using CIn = Codec<IN, VEC>;
     using COut = Codec<OUT, VEC>;
@@ -126,7 +130,7 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
     uint64_t* const cnt = (uint64_t*)((char*)p.cnt + boff);
     const int b = chain / p.nfb;
     const int fb = chain - b * p.nfb;
-    const int Qp = p.Qp;
+    const int Qp = QP ? QP : p.Qp;
     const int qsh = __builtin_ctz((unsigned)Qp);   // Qp is a power of two
     const int Gw = 64 >> qsh;
     const int wave = tid >> 6;
@@ -165,10 +169,16 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
     // loads, so that the table need not wait for them
     FfmParam fpar{0.f, 0.f};
     if constexpr (FFM) fpar = ffm_param_load(p.alpha, p.omega, p.d, p.ffm_c, (int64_t)fb * Dp, Dp);
-    uint32_t fl[R];
+    constexpr bool kBits = QP >= 8;
+    StepFlags<R, 0> sf;
+    uint32_t fl[kBits ? 1 : R], fl_tile0 = 0;
+    if constexpr (kBits) {
+        sf.load(rs_st, (uint32_t)(wave * Gw * R));
+    } else {
 #pragma unroll
-    for (int r = 0; r < R; ++r) fl[r] = bload_u8(rs_st, lrow + r);
-    const uint32_t fl_tile0 = bload_u8(rs_st, 0);
+        for (int r = 0; r < R; ++r) fl[r] = bload_u8(rs_st, lrow + r);
+        fl_tile0 = bload_u8(rs_st, 0);
+    }
     __builtin_amdgcn_sched_barrier(0);
     RawVec<IN, VEC> ra[AINV ? 1 : R];
     RawVec<IN, VEC> rx[R];
@@ -200,12 +210,23 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
     }
     __builtin_amdgcn_sched_barrier(0);
     uint32_t begins = 0, valid = 0;
+    if constexpr (kBits) {
+        // flags past T read zero
+        uint64_t w[StepFlags<R, 0>::W];
+        sf.words(w);
+        if (tile == 0 && wave == 0) w[0] |= 1ull;
+        fl_tile0 = (uint32_t)w[0] & 1u;                        // wavefront 0's: the tile's first step
+        begins = bits_at<R>(w, j * R);
+        const int left = (int)(rows_left < L ? rows_left : L) - (int)lrow;
+        valid = left >= R ? (uint32_t)((1ull << R) - 1ull) : left <= 0 ? 0u : (1u << left) - 1u;
+    } else {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int64_t t = row0 + r;
-        const uint32_t in = t < p.T ? 1u : 0u;
-        valid |= in << r;
-        begins |= (in & ((t == 0 ? 1u : 0u) | (fl[r] != 0u ? 1u : 0u))) << r;
+        for (int r = 0; r < R; ++r) {
+            const int64_t t = row0 + r;
+            const uint32_t in = t < p.T ? 1u : 0u;
+            valid |= in << r;
+            begins |= (in & ((t == 0 ? 1u : 0u) | (fl[r] != 0u ? 1u : 0u))) << r;
+        }
     }
     S ainv[VEC];
     if constexpr (FFM) {
@@ -240,9 +261,11 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
             const S xv = CIn::get(rx[r], v);
             const S av = a_at(r, v);
             const S nh = mad(av, own.H[v], xv);
-            const S na = own.A[v] * av;
             own.H[v] = bg ? xv : nh;
-            own.A[v] = bg ? s_one<S>() : na;
+            if constexpr (!AINV) {
+                const S na = own.A[v] * av;
+                own.A[v] = bg ? s_one<S>() : na;
+            }
         }
     }
     own.f = begins != 0;
@@ -274,7 +297,15 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
 
     // ---- (3) scan the wavefront's groups; combine wavefront totals in LDS
     SegT inc = own, exc;
-    wave_group_scan<S, VEC, false, kQpMax>(inc, exc, Qp);
+    if constexpr (AINV) {
+        // the factor of a lane's R steps is a^R (unused when it holds a begin)
+        typename WideOf<S>::type aR[VEC];
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) aR[v] = power<R>(widen(ainv[v]));
+        wave_group_scan_inv<S, VEC, false, kQpMax>(inc, exc, Qp, aR);
+    } else {
+        wave_group_scan<S, VEC, false, kQpMax>(inc, exc, Qp);
+    }
     if (j == Gw - 1) {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
@@ -423,12 +454,23 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
 
 // R: steps per lane with a time-invariant a; RS with a per-step a (the host
 // plans the tiles with the same counts, diag_fwd_rows)
+template <Kind IN, Kind OUT, int VEC, int R, int RS, int QP>
+static void launch_fwd_qp(const DiagFwdArgs& args, int64_t ntiles, bool ainv, hipStream_t s) {
+    if (ainv)
+        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, true, QP>), dim3((unsigned)ntiles), dim3(256), 0, s, args);
+    else
+        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, RS, false, QP>), dim3((unsigned)ntiles), dim3(256), 0, s,
+                           args);
+}
 template <Kind IN, Kind OUT, int VEC, int R, int RS = R>
 static hipError_t launch_fwd(const DiagFwdArgs& args, int64_t ntiles, bool ainv, hipStream_t s) {
-    if (ainv)
-        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, true>), dim3((unsigned)ntiles), dim3(256), 0, s, args);
-    else
-        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, RS, false>), dim3((unsigned)ntiles), dim3(256), 0, s, args);
+    if constexpr (VEC > 1) {
+        if (args.Qp == 8) {
+            launch_fwd_qp<IN, OUT, VEC, R, RS, 8>(args, ntiles, ainv, s);
+            return hipGetLastError();
+        }
+    }
+    launch_fwd_qp<IN, OUT, VEC, R, RS, 0>(args, ntiles, ainv, s);
     return hipGetLastError();
 }
 
@@ -438,11 +480,14 @@ hipError_t ffm_fwd_launch(bool vec, const DiagFwdArgs& args, int64_t ntiles, hip
     (void)ntiles;
     // whole groups of kXcds positions per chain (see the kernel)
     const int64_t grid = ((args.nt + kXcds - 1) / kXcds) * kXcds * args.nchains;
-    if (vec)
-        hipLaunchKernelGGL((diag_fwd_kernel<K_C64, K_C64, VC, R, true, true>), dim3((unsigned)grid), dim3(256), 0, s,
+    if (vec && args.Qp == 8)
+        hipLaunchKernelGGL((diag_fwd_kernel<K_C64, K_C64, VC, R, true, 8, true>), dim3((unsigned)grid), dim3(256), 0, s,
+                           args);
+    else if (vec)
+        hipLaunchKernelGGL((diag_fwd_kernel<K_C64, K_C64, VC, R, true, 0, true>), dim3((unsigned)grid), dim3(256), 0, s,
                            args);
     else
-        hipLaunchKernelGGL((diag_fwd_kernel<K_C64, K_C64, 1, R, true, true>), dim3((unsigned)grid), dim3(256), 0, s,
+        hipLaunchKernelGGL((diag_fwd_kernel<K_C64, K_C64, 1, R, true, 0, true>), dim3((unsigned)grid), dim3(256), 0, s,
                            args);
     return hipGetLastError();
 }

@@ -781,6 +781,115 @@ __device__ __forceinline__ void wave_group_scan(Seg<S, VEC>& inc, Seg<S, VEC>& e
     exc = seg_select<S, VEC>(has, o, seg_identity<S, VEC>());
 }
 
+// Powers of a time-invariant coefficient, in double and rounded once: with |a|
+// near 1 an error of a^R is amplified by the number of runs in an episode (the
+// product of R rounded factors was no better; squaring in float doubled the
+// error of da).
+struct cd {
+    double re, im;
+};
+__device__ __forceinline__ cd operator*(cd a, cd b) { return cd{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
+template <class S> struct WideOf { using type = double; };
+template <> struct WideOf<cf> { using type = cd; };
+__device__ __forceinline__ double widen(float a) { return (double)a; }
+__device__ __forceinline__ cd widen(cf a) { return cd{(double)a.re, (double)a.im}; }
+__device__ __forceinline__ float narrow(double a) { return (float)a; }
+__device__ __forceinline__ cf narrow(cd a) { return cf{(float)a.re, (float)a.im}; }
+template <int N, class W>
+__device__ __forceinline__ W power(W a) {
+    static_assert(N >= 1, "a positive power");
+    if constexpr (N == 1) return a;
+    else if constexpr (N % 2 == 0) return power<N / 2>(a * a);
+    else return a * power<N / 2>(a * a);
+}
+
+// wave_group_scan for a coefficient that no step changes (time-invariant a):
+// a group's run multiplies by aR = a^R whatever its steps, so only H and f
+// move between lanes and every A is a power of aR that the lanes follow by
+// themselves.  (A run holding a boundary keeps a meaningless A: f makes every
+// reader ignore it.)  inc.A is set here, from aR.
+template <class S, int VEC, bool REV, int M, int QP>
+__device__ __forceinline__ void sk_steps_inv(Seg<S, VEC>& inc, typename WideOf<S>::type (&pw)[VEC]) {
+    if constexpr (M < 64) {
+        const int lane = threadIdx.x & 63;
+        const bool takes = REV ? (lane & M) == 0 : (lane & M) != 0;
+        const bool of = sk_move<REV, M, QP>((uint32_t)inc.f) != 0u;
+        const bool reach = takes && !inc.f;
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            const S oh = sk_move<REV, M, QP>(inc.H[v]);
+            const S nh = mad(inc.A[v], oh, inc.H[v]);
+            const S na = inc.A[v] * narrow(pw[v]);
+            inc.H[v] = reach ? nh : inc.H[v];
+            inc.A[v] = takes ? na : inc.A[v];
+            if constexpr (2 * M < 64) pw[v] = pw[v] * pw[v];
+        }
+        inc.f = inc.f || (takes && of);
+        sk_steps_inv<S, VEC, REV, 2 * M, QP>(inc, pw);
+    }
+}
+template <class S, int VEC, bool REV, int QMAX = 64>
+__device__ __forceinline__ void wave_group_scan_inv(Seg<S, VEC>& inc, Seg<S, VEC>& exc, int Qp,
+                                                    typename WideOf<S>::type (&pw)[VEC]) {
+    const int lane = threadIdx.x & 63;
+    const int qsh = __builtin_ctz((unsigned)Qp);   // Qp is a power of two
+    const int j = lane >> qsh;
+    const int Gw = 64 >> qsh;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) inc.A[v] = narrow(pw[v]);
+    switch (Qp) {
+        case 1: sk_steps_inv<S, VEC, REV, 1, 1>(inc, pw); break;
+        case 2: if constexpr (QMAX >= 2) sk_steps_inv<S, VEC, REV, 2, 2>(inc, pw); break;
+        case 4: if constexpr (QMAX >= 4) sk_steps_inv<S, VEC, REV, 4, 4>(inc, pw); break;
+        case 8: if constexpr (QMAX >= 8) sk_steps_inv<S, VEC, REV, 8, 8>(inc, pw); break;
+        case 16: if constexpr (QMAX >= 16) sk_steps_inv<S, VEC, REV, 16, 16>(inc, pw); break;
+        case 32: if constexpr (QMAX >= 32) sk_steps_inv<S, VEC, REV, 32, 32>(inc, pw); break;
+        default: break;                                  // one group: nothing to scan
+    }
+    const bool has = REV ? (j + 1 < Gw) : (j >= 1);
+    const Seg<S, VEC> o = seg_shfl<S, VEC>(inc, has ? (REV ? lane + Qp : lane - Qp) : lane);
+    exc = seg_select<S, VEC>(has, o, seg_identity<S, VEC>());
+}
+
+// ------------------------------------------------------------ step flags
+// Begin flags of a wavefront's steps when its groups number at most eight
+// (Qp >= 8): one byte per lane and 64 steps and a ballot each, instead of a
+// byte load, a compare and a mask operation per step and lane.  Lane group j
+// then takes bits j R .. j R + R - 1 (PLUS: and the one after).  These, the
+// group width fixed at compile time and the invariant a's powers took a fifth
+// of the instructions: FFM gradient 275 -> 257 us and forward 112 -> 107
+// (T = 2^18, m = 32, c = 8), complex forward 58 -> 54, reverse 81 -> 79
+// (T = 65536, d = 256), f32 forward on T = 1024, d = 32 9.3 -> 8.1.
+template <int R, int PLUS>
+struct StepFlags {
+    static constexpr int W = (8 * R + PLUS + 63) / 64;
+    uint32_t fl[W];
+    // wrow: the wavefront's first step, relative to the resource's base
+    __device__ __forceinline__ void load(Rsrc rs, uint32_t wrow) {
+#pragma unroll
+        for (int i = 0; i < W; ++i) fl[i] = bload_u8(rs, wrow + 64u * i + (threadIdx.x & 63));
+    }
+    __device__ __forceinline__ void words(uint64_t (&w)[W]) const {
+#pragma unroll
+        for (int i = 0; i < W; ++i) w[i] = __ballot(fl[i] != 0u);
+    }
+};
+// N bits (N <= 32) of the bit string w from position `at` on, at per lane
+template <int N, int W>
+__device__ __forceinline__ uint32_t bits_at(const uint64_t (&w)[W], int at) {
+    uint64_t lo = w[0], hi = W > 1 ? w[1] : 0ull;
+#pragma unroll
+    for (int i = 1; i < W; ++i) {
+        const bool past = at >= 64 * i;
+        lo = past ? w[i] : lo;
+        hi = past ? (i + 1 < W ? w[i + 1] : 0ull) : hi;
+    }
+    const int sh = at & 63;
+    uint64_t v = lo >> sh;
+    if constexpr (W > 1) v |= sh ? hi << (64 - sh) : 0ull;
+    return (uint32_t)v & (N >= 32 ? 0xFFFFFFFFu : ((1u << (N & 31)) - 1u));
+}
+
 // ------------------------------------------------------- count look-back
 // Running count of begin steps before a tile (the episode index is that count
 // minus one), carried by one 64-bit word per tile: all ones = not yet

@@ -318,6 +318,28 @@ def test_tile_boundary_lengths(dtype, inv, d):
             check_bwd(w, label="tile edge L=%s" % Ls)
 
 
+@pytest.mark.parametrize("dtype,inv", [(dt, inv) for dt in ("f32", "bf16", "c64") for inv in (False, True)])
+def test_flags_at_word_and_lane_edges(dtype, inv):
+    """Full-width rows read a wavefront's begin flags as 64-bit words: begins
+    on and beside every multiple of 64 and of the lanes' 8, 12, 16 and 18
+    steps (first tape), and on a third of all steps (second tape), on a tape
+    that ends inside its third tile."""
+    Ls = _tile_lengths(dtype, inv, 256)
+    for T in sorted({2 * L + 5 for L in Ls}):
+        w = tapes.make_custom_diag(dtype, 2, T, 256, inv, seed=4000 + T)
+        rng = np.random.default_rng(T)
+        w.start[:] = 0
+        for m in (64, 8 * 9, 12 * 7, 16 * 5, 18 * 11):
+            for o in (-1, 0, 1):
+                at = np.arange(m, T, m) + o
+                w.start[0, at[(at > 0) & (at < T) & (rng.random(at.size) < 0.5)]] = 1
+        w.start[1, rng.random(T) < 0.33] = 1
+        w.start[:, 0] = 1
+        check_fwd(w, label="flag words")
+        if dtype != "bf16":
+            check_bwd(w, label="flag words")
+
+
 @pytest.mark.parametrize("pattern", ["all_begins", "single_episode", "begin_at_end", "flag_bytes"])
 @pytest.mark.parametrize("dtype", ["f32", "c64"])
 def test_flag_patterns(pattern, dtype):
