@@ -719,6 +719,7 @@ int lin_states(const float* k, const float* v, const uint8_t* start, int64_t T, 
     sa.fill = (u32x4*)ws;
     sa.fill16 = (int64_t)(p.off_states / 16);
     if (linattn_summary_launch(sa, p.nseg, s) != hipSuccess) return MEMOROID_EHIP;
+    if (p.nseg <= kLinDirectSegs) return MEMOROID_OK;
     LinScanArgs ca{};
     ca.states = sa.states;
     ca.R = sa.R;
@@ -766,6 +767,8 @@ int memoroid_scan_linattn(const float* q, const float* k, const float* v, const 
     oa.v = v;
     oa.start = start;
     oa.states = (const float*)(ws + p.off_states);
+    oa.R = (const uint8_t*)(ws + p.off_R);
+    oa.nseg = p.nseg;
     oa.out = out;
     oa.T = T;
     oa.H = H;
@@ -848,6 +851,7 @@ int memoroid_scan_linattn_bwd(const float* q, const float* k, const float* v, co
     ba.g = grad_out;
     ba.start = start;
     ba.states = (const float*)(ws + f.off_states);
+    ba.R = (const uint8_t*)(ws + f.off_R);
     ba.rstates = (float*)(ws + p.off_rstates);
     ba.rden = (float*)(ws + p.off_rden);
     ba.dden = (float*)(ws + p.off_dden);
@@ -862,12 +866,14 @@ int memoroid_scan_linattn_bwd(const float* q, const float* k, const float* v, co
 
     // scan of the reverse summaries: Y_c = dU_c + [segment c holds no begin
     // step] Y_{c+1}
-    LinScanArgs ca{};
-    ca.states = ba.rstates;
-    ca.R = (const uint8_t*)(ws + f.off_R);
-    ca.n = f.nseg;
-    ca.width = f.width;
-    if (linattn_scan_launch(true, ca, s) != hipSuccess) return MEMOROID_EHIP;
+    if (f.nseg > kLinDirectSegs) {
+        LinScanArgs ca{};
+        ca.states = ba.rstates;
+        ca.R = ba.R;
+        ca.n = f.nseg;
+        ca.width = f.width;
+        if (linattn_scan_launch(true, ca, s) != hipSuccess) return MEMOROID_EHIP;
+    }
     return check_hip(linattn_dkv_launch(ba, s));
 }
 

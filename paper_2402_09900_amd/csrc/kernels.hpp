@@ -181,6 +181,14 @@ hipError_t store_i64_launch(int64_t* p, int64_t v, hipStream_t s);
 // kLinStateWords floats, one per (segment, head).
 constexpr int kLinChunkRows = 64;
 constexpr int kLinStateWords = 64 * 64 + 64;
+// Up to this many segments the kernels add up the states they need themselves
+// and no scan is launched.  At 8 that is faster whatever the flags: T = 512, 4
+// heads, forward / gradient 17.2 / 35.7 -> 14.6 / 29.9 us with episodes of 100
+// steps, 15.4 / 34.1 with one episode.  At 16 (T = 1000) it is 15.3 / 32.4
+// against 17.7 / 37.0 with short episodes but 17.5 / 42.6 with one episode,
+// where every workgroup reads up to 15 states that other XCDs wrote.
+constexpr int kLinDirectSegs = 8;
+static_assert(kLinDirectSegs <= 64, "a segment's flag is a bit of a 64-bit word");
 
 struct LinSummaryArgs {
     const float* k;
@@ -207,10 +215,12 @@ struct LinOutputArgs {
     const float* k;
     const float* v;
     const uint8_t* start;
-    const float* states;   // scanned states, [segments][H][kLinStateWords]
+    const float* states;   // scanned states, [segments][H][kLinStateWords] (at most kLinDirectSegs: summaries)
+    const uint8_t* R;      // [segments] segment holds a begin step
     float* out;
     int64_t T;
     int64_t H;
+    int64_t nseg;
     int32_t chunks;
     int32_t* idx;       // episode index out [T], or NULL
     uint64_t* cnt;      // [segments] begin-count words (filled by the summary kernel)
@@ -228,8 +238,9 @@ struct LinBwdArgs {
     const float* out;      // forward readout [T][H][64]
     const float* g;        // dL/dout [T][H][64]
     const uint8_t* start;
-    const float* states;   // scanned forward states
-    float* rstates;        // reverse summaries, scanned in between
+    const float* states;   // scanned forward states (at most kLinDirectSegs: summaries)
+    const uint8_t* R;      // [segments] segment holds a begin step
+    float* rstates;        // reverse summaries, scanned in between (likewise)
     float* rden;           // workspace [T][H]
     float* dden;           // workspace [T][H]
     float* dq;

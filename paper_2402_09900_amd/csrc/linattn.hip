@@ -185,6 +185,7 @@ __global__ __launch_bounds__(256) void state_scan_kernel(LinScanArgs p) {
 // the own block, z and den) that two wavefronts per SIMD only partly overlap.
 // Loading V a phase earlier (43 us) or a branch-free path for chunks without
 // begin steps (41 us) gained nothing.
+template <bool DIRECT>
 __global__ __launch_bounds__(256, 3) void linattn_output_kernel(LinOutputArgs p) {
     __shared__ __attribute__((aligned(16))) float sQ[kTileF];     // phi(Q)
     __shared__ __attribute__((aligned(16))) float sK[kTileF];     // phi(K)
@@ -216,9 +217,19 @@ __global__ __launch_bounds__(256, 3) void linattn_output_kernel(LinOutputArgs p)
     };
     fetch_qk(0);
     Frag st;                                   // st[s][r] = S[16 r + 4 g + s][16 w + c]
-    const Rsrc rs_s = state_rows(p.states, seg - 1, p.H, h, seg > 0);
-    load_state_kd(st, rs_s, L);
-    const float z_in = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_s, (kDim * kDim + L.lane) * 4, 0, 0));
+    float z_in = 0.0f;
+    state_before<DIRECT, false>(
+        p.states, p.R, seg, p.nseg, p.H, h,
+        [&](Rsrc rs) {
+            load_state_kd(st, rs, L);
+            z_in = state_z1(rs, L.lane);
+        },
+        [&](Rsrc rs) {
+            Frag s;
+            load_state_kd(s, rs, L);
+            z_in += state_z1(rs, L.lane);
+            add_frag(st, s);
+        });
     fetch_v(0);
     if (L.w == 0) sZ[4][L.lane] = z_in;
 
@@ -359,7 +370,9 @@ hipError_t linattn_scan_launch(bool rev, const LinScanArgs& a, hipStream_t s) {
 }
 
 hipError_t linattn_output_launch(const LinOutputArgs& a, int64_t nseg, hipStream_t s) {
-    hipLaunchKernelGGL(linattn_output_kernel, dim3((unsigned)nseg, (unsigned)a.H), dim3(256), 0, s, a);
+    const dim3 grid((unsigned)nseg, (unsigned)a.H), block(256);
+    if (nseg <= kLinDirectSegs) hipLaunchKernelGGL(linattn_output_kernel<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(linattn_output_kernel<false>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -28,6 +28,7 @@ namespace memoroid {
 // T = 32768, 4 heads: 58 us, 240 MFMAs a chunk and wavefront (26 us of the
 // matrix cores); a separate backward-summary kernel and a dq product beside dk
 // and dv took 43 us and a good third of 108.
+template <bool DIRECT>
 __global__ __launch_bounds__(256, 2) void linattn_dq_kernel(LinBwdArgs p) {
     __shared__ __attribute__((aligned(16))) float sQ[kTileF], sK[kTileF], sV[kTileF], sD[kTileF];
     __shared__ f32x4 sP[4][64];                                   // each block's masked dP, as mul_rows returns it
@@ -61,9 +62,19 @@ __global__ __launch_bounds__(256, 2) void linattn_dq_kernel(LinBwdArgs p) {
     fetch_qkv(0);
     fetch_go(0);
     Frag st, us;                               // st[s][r] = S[16 w + c][16 r + 4 g + s], us the same of U
-    const Rsrc rs_s = state_rows(p.states, seg - 1, p.H, h, seg > 0);
-    load_state_n(st, rs_s, L);
-    const float z_in = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_s, (kDim * kDim + L.lane) * 4, 0, 0));
+    float z_in = 0.0f;
+    state_before<DIRECT, false>(
+        p.states, p.R, seg, p.nseg, p.H, h,
+        [&](Rsrc rs) {
+            load_state_n(st, rs, L);
+            z_in = state_z1(rs, L.lane);
+        },
+        [&](Rsrc rs) {
+            Frag s;
+            load_state_n(s, rs, L);
+            z_in += state_z1(rs, L.lane);
+            add_frag(st, s);
+        });
     if (L.w == 0) sZ[4][L.lane] = z_in;
 #pragma unroll
     for (int s = 0; s < 4; ++s) us[s] = zero4();
@@ -209,6 +220,7 @@ __global__ __launch_bounds__(256, 2) void linattn_dq_kernel(LinBwdArgs p) {
 // take).  T = 32768, 4 heads: 61 us, 320 MFMAs a chunk and wavefront, matrix
 // cores 62 % busy (54 us with every load served by the L2, 46 us with the
 // MFMAs replaced by single FMAs).
+template <bool DIRECT>
 __global__ __launch_bounds__(256, 2) void linattn_dkv_kernel(LinBwdArgs p) {
     __shared__ __attribute__((aligned(16))) float sQ[kTileF], sK[kTileF], sV[kTileF], sD[kTileF];
     __shared__ f32x4 sP[4][64], sA[4][64];                        // each block's masked dP and A
@@ -238,10 +250,23 @@ __global__ __launch_bounds__(256, 2) void linattn_dkv_kernel(LinBwdArgs p) {
     };
     fetch(nch - 1);
     Frag uk, uv;                               // uk[s][r] = U[16 w + c][16 r + 4 g + s], uv[s][r] = U[16 r + 4 g + s][16 w + c]
-    const Rsrc rs_u = state_rows(p.rstates, seg + 1, p.H, h, seg + 1 < p.nseg);
-    load_state_n(uk, rs_u, L);
-    load_state_kd(uv, rs_u, L);
-    f32x4 wz = bload4(rs_u, (uint32_t)(kDim * kDim + 16 * L.w + 4 * L.g) * 4u);
+    f32x4 wz = zero4();
+    const int wat = 16 * L.w + 4 * L.g;
+    state_before<DIRECT, true>(
+        p.rstates, p.R, seg, p.nseg, p.H, h,
+        [&](Rsrc rs) {
+            load_state_n(uk, rs, L);
+            load_state_kd(uv, rs, L);
+            wz = state_z4(rs, wat);
+        },
+        [&](Rsrc rs) {
+            Frag sk, sv;
+            load_state_n(sk, rs, L);
+            load_state_kd(sv, rs, L);
+            wz += state_z4(rs, wat);
+            add_frag(uk, sk);
+            add_frag(uv, sv);
+        });
 
 #pragma unroll 1
     for (int ch = nch - 1; ch >= 0; --ch) {
@@ -341,12 +366,16 @@ __global__ __launch_bounds__(256, 2) void linattn_dkv_kernel(LinBwdArgs p) {
 }
 
 hipError_t linattn_dq_launch(const LinBwdArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(linattn_dq_kernel, dim3((unsigned)a.nseg, (unsigned)a.H), dim3(256), 0, s, a);
+    const dim3 grid((unsigned)a.nseg, (unsigned)a.H), block(256);
+    if (a.nseg <= kLinDirectSegs) hipLaunchKernelGGL(linattn_dq_kernel<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(linattn_dq_kernel<false>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 
 hipError_t linattn_dkv_launch(const LinBwdArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(linattn_dkv_kernel, dim3((unsigned)a.nseg, (unsigned)a.H), dim3(256), 0, s, a);
+    const dim3 grid((unsigned)a.nseg, (unsigned)a.H), block(256);
+    if (a.nseg <= kLinDirectSegs) hipLaunchKernelGGL(linattn_dkv_kernel<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(linattn_dkv_kernel<false>, grid, block, 0, s, a);
     return hipGetLastError();
 }
 

@@ -302,6 +302,33 @@ __device__ __forceinline__ void load_state_n(Frag& st, Rsrc rs, const LinLane& L
         for (int s = 0; s < 4; ++s) st[s][r] = v[s];
     }
 }
+// The state before segment `seg` (REV: after it): load(rs) reads the
+// neighbour's scanned state or, DIRECT (at most kLinDirectSegs segments), its
+// summary, to which add(rs) adds the others back to the nearest segment that
+// holds a begin step, found with one ballot over the flags.
+template <bool DIRECT, bool REV, class Load, class Add>
+__device__ __forceinline__ void state_before(const float* states, const uint8_t* R, int64_t seg, int64_t nseg, int64_t H,
+                                             int64_t h, Load&& load, Add&& add) {
+    const bool any = REV ? seg + 1 < nseg : seg > 0;
+    const int64_t near = REV ? seg + 1 : seg - 1;
+    load(state_rows(states, near, H, h, any));
+    if (!DIRECT || !any) return;
+    const uint32_t fl = bload_u8(make_rsrc(R, nseg), threadIdx.x & 63);
+    const uint64_t holds = __ballot(fl != 0u);          // segments with a begin step
+    const uint64_t m = REV ? holds & ~((1ull << near) - 1ull) : holds & ((2ull << near) - 1ull);
+    const int far = m ? (REV ? __builtin_ctzll(m) : 63 - __builtin_clzll(m)) : (REV ? (int)nseg - 1 : 0);
+    const int more = REV ? far - (int)near : (int)near - far;
+#pragma unroll 2
+    for (int i = 1; i <= more; ++i) add(state_rows(states, REV ? near + i : near - i, H, h, true));
+}
+__device__ __forceinline__ void add_frag(Frag& a, const Frag& b) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a[s] += b[s];
+}
+__device__ __forceinline__ float state_z1(Rsrc rs, int i) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (kDim * kDim + i) * 4, 0, 0));
+}
+__device__ __forceinline__ f32x4 state_z4(Rsrc rs, int i) { return bload4(rs, (uint32_t)(kDim * kDim + i) * 4u); }
 __device__ __forceinline__ void store_state_n(float* p, const Frag& st, const LinLane& L) {
 #pragma unroll
     for (int r = 0; r < 4; ++r)

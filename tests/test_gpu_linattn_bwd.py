@@ -71,6 +71,19 @@ def test_segment_lengths_and_scan_rounds(T, H):
     check(tapes.make_linattn(3, seed=500 + H, T=T, H=H), "segments")
 
 
+@pytest.mark.parametrize("T", [64 * 2, 64 * 8 - 5, 64 * 8, 64 * 8 + 1])
+@pytest.mark.parametrize("begins", [(), (70,), (0, 63, 64, 65, 400)])
+def test_few_segments_add_up_states(T, begins):
+    """Up to eight segments: every workgroup adds up the summaries back (and,
+    in reverse, ahead) to the nearest segment with a begin step -- one episode
+    over all of them, one begin step early, begins at segment edges; one
+    segment more takes the scan."""
+    la = tapes.make_linattn(3, seed=600 + T, T=T, H=2)
+    f = np.zeros(T, np.uint8)
+    f[[b for b in begins if b < T]] = 1
+    check(_with_flags(la, f), "few segments")
+
+
 def _with_flags(la, flags):
     la.start = flags.astype(np.uint8)
     return la
