@@ -47,7 +47,9 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
     __shared__ uint32_t sWF[NW];
     __shared__ S sCarry[64 * VEC];
     __shared__ LookbackLds<S, VEC> sLb;
-    __shared__ cf sFfm[FFM ? 64 : 1];      // FFM conj(a) of the chain's features
+    // powers of the lane factor that the wavefront's scan asks for (FFM)
+    constexpr int kPowers = QP == 8 ? 3 : 6;
+    __shared__ cf sFfm[FFM ? (1 + kPowers) * kFfmCols : 1];      // FFM conj(a) of the features, then its powers
 
     const int tid = threadIdx.x;
     // the workgroup's chain is fixed by its index (each run of nchains
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
         // conj(a) of the chain's features, evaluated once per tile as in the
         // forward pass
         if constexpr (std::is_same<S, cf>::value) {
-            ffm_table_store(sFfm, fpar, Dp, true);
+            ffm_table_store<R, kPowers>(sFfm, fpar, Dp, true);
             barrier_lds();
 #pragma unroll
             for (int v = 0; v < VEC; ++v) ainv[v] = sFfm[q * VEC + v];
@@ -277,10 +279,15 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
     SegT inc = own, exc;
     if constexpr (AINV) {
         // the factor of a lane's R steps is a^R (unused when it holds an end)
-        typename WideOf<S>::type aR[VEC];
+        if constexpr (FFM) {
+            TablePowers<S, VEC> pw{sFfm + kFfmCols + q * VEC};
+            wave_group_scan_inv<S, VEC, true, kQpMax>(inc, exc, Qp, pw);
+        } else {
+            LanePowers<S, VEC> pw;
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) aR[v] = power<R>(widen(ainv[v]));
-        wave_group_scan_inv<S, VEC, true, kQpMax>(inc, exc, Qp, aR);
+            for (int v = 0; v < VEC; ++v) pw.p[v] = power<R>(widen(ainv[v]));
+            wave_group_scan_inv<S, VEC, true, kQpMax>(inc, exc, Qp, pw);
+        }
     } else {
         wave_group_scan<S, VEC, true, kQpMax>(inc, exc, Qp);
     }

@@ -79,7 +79,9 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
     __shared__ LookbackLds<S, VEC> sLb;
     __shared__ uint32_t sWC[NW];           // begin counts per wavefront (episode index)
     __shared__ uint32_t sCntBefore;        // begins on the tape before this tile
-    __shared__ cf sFfm[FFM ? 64 : 1];      // FFM transitions of the chain's features
+    // powers of the lane factor that the wavefront's scan asks for (FFM)
+    constexpr int kPowers = QP == 8 ? 3 : 6;
+    __shared__ cf sFfm[FFM ? (1 + kPowers) * kFfmCols : 1];      // FFM transitions of the features, then their powers
 
     const int tid = threadIdx.x;
     // the workgroup's chain is fixed by its index (each run of nchains
@@ -233,7 +235,7 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
         // the chain's transitions, evaluated once per tile by wavefront 0
         // while the loads are in flight
         if constexpr (std::is_same<S, cf>::value) {
-            ffm_table_store(sFfm, fpar, Dp, false);
+            ffm_table_store<R, kPowers>(sFfm, fpar, Dp, false);
             barrier_lds();
 #pragma unroll
             for (int v = 0; v < VEC; ++v) ainv[v] = sFfm[q * VEC + v];
@@ -299,10 +301,15 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
     SegT inc = own, exc;
     if constexpr (AINV) {
         // the factor of a lane's R steps is a^R (unused when it holds a begin)
-        typename WideOf<S>::type aR[VEC];
+        if constexpr (FFM) {
+            TablePowers<S, VEC> pw{sFfm + kFfmCols + q * VEC};
+            wave_group_scan_inv<S, VEC, false, kQpMax>(inc, exc, Qp, pw);
+        } else {
+            LanePowers<S, VEC> pw;
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) aR[v] = power<R>(widen(ainv[v]));
-        wave_group_scan_inv<S, VEC, false, kQpMax>(inc, exc, Qp, aR);
+            for (int v = 0; v < VEC; ++v) pw.p[v] = power<R>(widen(ainv[v]));
+            wave_group_scan_inv<S, VEC, false, kQpMax>(inc, exc, Qp, pw);
+        }
     } else {
         wave_group_scan<S, VEC, false, kQpMax>(inc, exc, Qp);
     }

@@ -467,15 +467,42 @@ template <> struct Desc<cf> {
     }
 };
 
+// Powers of a time-invariant coefficient, in double and rounded once: with |a|
+// near 1 an error of a^R is amplified by the number of runs in an episode (the
+// product of R rounded factors was no better; squaring in float doubled the
+// error of da).
+struct cd {
+    double re, im;
+};
+__device__ __forceinline__ cd operator*(cd a, cd b) { return cd{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
+template <class S> struct WideOf { using type = double; };
+template <> struct WideOf<cf> { using type = cd; };
+__device__ __forceinline__ double widen(float a) { return (double)a; }
+__device__ __forceinline__ cd widen(cf a) { return cd{(double)a.re, (double)a.im}; }
+__device__ __forceinline__ float narrow(double a) { return (float)a; }
+__device__ __forceinline__ cf narrow(cd a) { return cf{(float)a.re, (float)a.im}; }
+
+template <int N, class W>
+__device__ __forceinline__ W power(W a) {
+    static_assert(N >= 1, "a positive power");
+    if constexpr (N == 1) return a;
+    else if constexpr (N % 2 == 0) return power<N / 2>(a * a);
+    else return a * power<N / 2>(a * a);
+}
+
 // FFM transition of a chain's Dp features, a_jk = exp(-|alpha_j|) (cos omega_k
-// + i sin omega_k) for feature f = j * c + k, evaluated once per tile: lane
-// l < Dp (Dp <= 64, so wavefront 0 alone) takes feature f_base + l, in double
-// and rounded once to float (with |a| near 1 the error of a is amplified by up
-// to the episode length), into tab[l].  conj_a stores conj(a) (the reverse
-// scan's coefficient).  Features past d get a valid, unused value.  The caller
-// synchronises the workgroup before reading tab.  Two steps, so that a
-// kernel can load the parameters first and evaluate the table while its
-// other loads are in flight.
+// + i sin omega_k) for feature f = j * c + k, and the powers of it that move
+// between lanes, evaluated once per tile: lane l < Dp (Dp <= 64, so wavefront
+// 0 alone) takes feature f_base + l, in double, each value rounded once to
+// float: row 0 is a, row 1 + i is a^(R 2^i).  (The powers of a rounded to
+// float first would amplify that rounding by the episode length: errors
+// against 64 bits 1.1e-6 for the states, 3.9e-6 for dalpha and 4.7e-6 for
+// domega instead of 4.0e-7, 7.1e-7 and 7.8e-7 at T = 2^18, m = 32, c = 8.)
+// conj_a takes conj(a) (the reverse scan's coefficient).  Features past d get
+// valid, unused values.  The caller synchronises the workgroup before reading
+// tab.  Two steps, so that a kernel can load the parameters first and evaluate
+// the table while its other loads are in flight.
+constexpr int kFfmCols = 64;
 struct FfmParam {
     float alpha, omega;
 };
@@ -491,14 +518,21 @@ __device__ __forceinline__ FfmParam ffm_param_load(const float* alpha, const flo
     }
     return r;
 }
+template <int R, int NP>
 __device__ __forceinline__ void ffm_table_store(cf* tab, FfmParam pr, int Dp, bool conj_a) {
     const int l = threadIdx.x;
     if (l < Dp) {
         const double mag = exp(-fabs((double)pr.alpha));
         double sn, cs;
         sincos((double)pr.omega, &sn, &cs);
-        const float im = (float)(mag * sn);
-        tab[l] = cf{(float)(mag * cs), conj_a ? -im : im};
+        const cd a{mag * cs, conj_a ? -mag * sn : mag * sn};
+        tab[l] = narrow(a);
+        cd pw = power<R>(a);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            tab[(1 + i) * kFfmCols + l] = narrow(pw);
+            pw = pw * pw;
+        }
     }
 }
 
@@ -781,35 +815,27 @@ __device__ __forceinline__ void wave_group_scan(Seg<S, VEC>& inc, Seg<S, VEC>& e
     exc = seg_select<S, VEC>(has, o, seg_identity<S, VEC>());
 }
 
-// Powers of a time-invariant coefficient, in double and rounded once: with |a|
-// near 1 an error of a^R is amplified by the number of runs in an episode (the
-// product of R rounded factors was no better; squaring in float doubled the
-// error of da).
-struct cd {
-    double re, im;
-};
-__device__ __forceinline__ cd operator*(cd a, cd b) { return cd{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re}; }
-template <class S> struct WideOf { using type = double; };
-template <> struct WideOf<cf> { using type = cd; };
-__device__ __forceinline__ double widen(float a) { return (double)a; }
-__device__ __forceinline__ cd widen(cf a) { return cd{(double)a.re, (double)a.im}; }
-__device__ __forceinline__ float narrow(double a) { return (float)a; }
-__device__ __forceinline__ cf narrow(cd a) { return cf{(float)a.re, (float)a.im}; }
-template <int N, class W>
-__device__ __forceinline__ W power(W a) {
-    static_assert(N >= 1, "a positive power");
-    if constexpr (N == 1) return a;
-    else if constexpr (N % 2 == 0) return power<N / 2>(a * a);
-    else return a * power<N / 2>(a * a);
-}
-
 // wave_group_scan for a coefficient that no step changes (time-invariant a):
 // a group's run multiplies by aR = a^R whatever its steps, so only H and f
 // move between lanes and every A is a power of aR that the lanes follow by
 // themselves.  (A run holding a boundary keeps a meaningless A: f makes every
-// reader ignore it.)  inc.A is set here, from aR.
-template <class S, int VEC, bool REV, int M, int QP>
-__device__ __forceinline__ void sk_steps_inv(Seg<S, VEC>& inc, typename WideOf<S>::type (&pw)[VEC]) {
+// reader ignore it.)  inc.A is set here, from aR.  pw(i, v) is aR^(2^i) of
+// feature v: by squaring (LanePowers) or from a table (TablePowers).
+template <class S, int VEC>
+struct LanePowers {
+    typename WideOf<S>::type p[VEC];               // p[v] = aR^(2^i) of the last i asked for
+    __device__ __forceinline__ S operator()(int i, int v) {
+        if (i > 0) p[v] = p[v] * p[v];
+        return narrow(p[v]);
+    }
+};
+template <class S, int VEC>
+struct TablePowers {
+    const S* tab;                                  // the lane's first feature of row 1 of ffm_table_store's table
+    __device__ __forceinline__ S operator()(int i, int v) const { return tab[i * kFfmCols + v]; }
+};
+template <class S, int VEC, bool REV, int M, int QP, int I, class P>
+__device__ __forceinline__ void sk_steps_inv(Seg<S, VEC>& inc, P& pw) {
     if constexpr (M < 64) {
         const int lane = threadIdx.x & 63;
         const bool takes = REV ? (lane & M) == 0 : (lane & M) != 0;
@@ -819,31 +845,29 @@ __device__ __forceinline__ void sk_steps_inv(Seg<S, VEC>& inc, typename WideOf<S
         for (int v = 0; v < VEC; ++v) {
             const S oh = sk_move<REV, M, QP>(inc.H[v]);
             const S nh = mad(inc.A[v], oh, inc.H[v]);
-            const S na = inc.A[v] * narrow(pw[v]);
+            const S na = inc.A[v] * pw(I, v);
             inc.H[v] = reach ? nh : inc.H[v];
             inc.A[v] = takes ? na : inc.A[v];
-            if constexpr (2 * M < 64) pw[v] = pw[v] * pw[v];
         }
         inc.f = inc.f || (takes && of);
-        sk_steps_inv<S, VEC, REV, 2 * M, QP>(inc, pw);
+        sk_steps_inv<S, VEC, REV, 2 * M, QP, I + 1>(inc, pw);
     }
 }
-template <class S, int VEC, bool REV, int QMAX = 64>
-__device__ __forceinline__ void wave_group_scan_inv(Seg<S, VEC>& inc, Seg<S, VEC>& exc, int Qp,
-                                                    typename WideOf<S>::type (&pw)[VEC]) {
+template <class S, int VEC, bool REV, int QMAX = 64, class P>
+__device__ __forceinline__ void wave_group_scan_inv(Seg<S, VEC>& inc, Seg<S, VEC>& exc, int Qp, P& pw) {
     const int lane = threadIdx.x & 63;
     const int qsh = __builtin_ctz((unsigned)Qp);   // Qp is a power of two
     const int j = lane >> qsh;
     const int Gw = 64 >> qsh;
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) inc.A[v] = narrow(pw[v]);
+    for (int v = 0; v < VEC; ++v) inc.A[v] = pw(0, v);
     switch (Qp) {
-        case 1: sk_steps_inv<S, VEC, REV, 1, 1>(inc, pw); break;
-        case 2: if constexpr (QMAX >= 2) sk_steps_inv<S, VEC, REV, 2, 2>(inc, pw); break;
-        case 4: if constexpr (QMAX >= 4) sk_steps_inv<S, VEC, REV, 4, 4>(inc, pw); break;
-        case 8: if constexpr (QMAX >= 8) sk_steps_inv<S, VEC, REV, 8, 8>(inc, pw); break;
-        case 16: if constexpr (QMAX >= 16) sk_steps_inv<S, VEC, REV, 16, 16>(inc, pw); break;
-        case 32: if constexpr (QMAX >= 32) sk_steps_inv<S, VEC, REV, 32, 32>(inc, pw); break;
+        case 1: sk_steps_inv<S, VEC, REV, 1, 1, 0>(inc, pw); break;
+        case 2: if constexpr (QMAX >= 2) sk_steps_inv<S, VEC, REV, 2, 2, 0>(inc, pw); break;
+        case 4: if constexpr (QMAX >= 4) sk_steps_inv<S, VEC, REV, 4, 4, 0>(inc, pw); break;
+        case 8: if constexpr (QMAX >= 8) sk_steps_inv<S, VEC, REV, 8, 8, 0>(inc, pw); break;
+        case 16: if constexpr (QMAX >= 16) sk_steps_inv<S, VEC, REV, 16, 16, 0>(inc, pw); break;
+        case 32: if constexpr (QMAX >= 32) sk_steps_inv<S, VEC, REV, 32, 32, 0>(inc, pw); break;
         default: break;                                  // one group: nothing to scan
     }
     const bool has = REV ? (j + 1 < Gw) : (j >= 1);
