@@ -1,6 +1,7 @@
 // abi.hip -- the extern "C" entry points declared in include/memoroid.h:
 // argument validation (before any HIP call), tiling plans, workspace layout
 // and kernel launches.
+#include <cmath>
 #include <limits.h>
 #include <atomic>
 #include <mutex>
@@ -208,6 +209,14 @@ void set_scan_ws(Args& a, const DiagPlan& p, char* base, WsHeader* hdr, uint64_t
     a.ctr = (uint32_t*)(base + p.off_ctr);
 }
 
+// Cache policy of a diagonal scan from its row of d features and the tensors it
+// reads (infinite: kStreamOut is no choice); kernels.hpp says why the lines lie
+// there.
+int cache_policy(int64_t row_bytes, double input_bytes) {
+    if (row_bytes % kChainRowBytes != 0) return kCached;
+    return input_bytes <= (double)kCachedInputBytes ? kStreamOut : kStreamAll;
+}
+
 bool diag_dtypes_ok(int in_dt, int out_dt) {
     return (in_dt == MEMOROID_F32 && out_dt == MEMOROID_F32) || (in_dt == MEMOROID_BF16 && out_dt == MEMOROID_BF16) ||
            (in_dt == MEMOROID_BF16 && out_dt == MEMOROID_F32) || (in_dt == MEMOROID_C64 && out_dt == MEMOROID_C64);
@@ -321,6 +330,7 @@ static int scan_diag_run(const void* a, int64_t a_stride_t, const void* x, const
     args.Qp = p.Qp;
     args.nfb = p.nfb;
     args.nchains = (int32_t)p.nchains;
+    args.policy = cache_policy(d * ib, (double)BTd * ib * (ainv ? 1 : 2));
     set_scan_ws(args, p, ws, (WsHeader*)ws, layout_sig({kSigDiag, B, T, d, sd, vec, ainv}));
     args.idx = episode_idx;
     args.cnt = (uint64_t*)(ws + p.off_cnt);
@@ -404,6 +414,7 @@ static int scan_ffm_run(const float* alpha, const float* omega, const float* x, 
     args.Qp = p.Qp;
     args.nfb = p.nfb;
     args.nchains = (int32_t)p.nchains;
+    args.policy = cache_policy(d * 8, (double)BTd / (double)c * 4);
     set_scan_ws(args, p, ws, (WsHeader*)ws, layout_sig({kSigFfm, B, T, m, c, vec}));
     args.idx = episode_idx;
     args.cnt = (uint64_t*)(ws + p.off_cnt);
@@ -515,6 +526,7 @@ static int scan_ffm_bwd_run(const float* alpha, const float* omega, const uint8_
     args.Qp = p.Qp;
     args.nfb = p.nfb;
     args.nchains = (int32_t)p.nchains;
+    args.policy = cache_policy(d * 8, INFINITY);
     set_scan_ws(args, p, ws, (WsHeader*)ws, layout_sig({kSigFfmBwd, B, T, m, c, vec, params}));
     args.alpha = alpha;
     args.omega = omega;
@@ -623,6 +635,7 @@ static int scan_diag_bwd_run(const void* a, int64_t a_stride_t, const uint8_t* s
     args.Qp = p.Qp;
     args.nfb = p.nfb;
     args.nchains = (int32_t)p.nchains;
+    args.policy = cache_policy(d * eb, ainv ? INFINITY : (double)BTd * eb * (grad_a ? 3 : 2));
     set_scan_ws(args, p, ws, (WsHeader*)ws,
                 layout_sig({kSigDiagBwd, B, T, d, dtype, vec, ainv, grad_a != nullptr}));
     const int k = dtype == MEMOROID_F32 ? K_F32 : K_C64;

@@ -26,11 +26,12 @@ namespace memoroid {
 // QP: the plan's lane-group width when it is fixed at compile time (8, a whole
 // chain row of vector-wide lanes), 0 when it comes from the plan, as in the
 // forward scan.
-template <Kind K, int VEC, int R, bool AINV, int QP, bool FFM = false>
+template <Kind K, int VEC, int R, bool AINV, int QP, int POL, bool FFM = false>
 __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
     static_assert(!FFM || (K == K_C64 && AINV), "FFM: complex state, generated a");
     static_assert(R >= 1 && R < 32, "a lane's steps (and the one after) are bits of 32-bit masks");
     static_assert(QP == 0 || QP == 8, "fixed group width: whole chain rows");
+    constexpr int kLd = POL == kStreamAll ? kNt : 0, kSt = POL != kCached ? kNt : 0;
     using S = typename StateOf<K>::type;
     using C = Codec<K, VEC>;
     using SegT = Seg<S, VEC>;
@@ -146,9 +147,9 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const uint32_t off = off0 + r * step;
-        raw_bload(rg[r], rs_g, off);
-        if constexpr (!AINV) raw_bload(ra[r], rs_a, off + step);
-        if (want_da) raw_bload(rh[r], rs_h, h_back ? off : off - step);
+        raw_bload<kLd>(rg[r], rs_g, off);
+        if constexpr (!AINV) raw_bload<kLd>(ra[r], rs_a, off + step);
+        if (want_da) raw_bload<kLd>(rh[r], rs_h, h_back ? off : off - step);
     }
     __builtin_amdgcn_sched_barrier(0);
     uint32_t ends = 0, begins = 0, valid = 0;
@@ -423,9 +424,9 @@ __global__ __launch_bounds__(256) void diag_bwd_kernel(DiagBwdArgs p) {
             const Rsrc rs_da = make_rsrc(AINV ? p.dx : (char*)p.da + tape_row0 * rowB, AINV ? 0 : rows_left * rowB);
 #pragma unroll
             for (int r = R - 1; r >= 0; --r) {
-                raw_bstore_nt(rs_dx, off0 + r * step, rg[r]);
+                raw_bstore<kSt>(rs_dx, off0 + r * step, rg[r]);
                 if constexpr (!AINV) {
-                    if (want_da) raw_bstore_nt(rs_da, off0 + r * step, ra[r]);
+                    if (want_da) raw_bstore<kSt>(rs_da, off0 + r * step, ra[r]);
                 }
             }
         }
@@ -549,16 +550,23 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float* in, float* out
 
 // ------------------------------------------------------------------ launch
 
+template <Kind K, int VEC, int R, bool AINV, int QP, bool FFM>
+static void launch_bwd_pol(const DiagBwdArgs& args, unsigned grid, hipStream_t s) {
+    const dim3 g(grid), block(256);
+    if (args.policy == kCached)
+        hipLaunchKernelGGL((diag_bwd_kernel<K, VEC, R, AINV, QP, kCached, FFM>), g, block, 0, s, args);
+    else if (QP == 0 || AINV || args.policy == kStreamAll)     // no kStreamOut for the rarer plans and an invariant a
+        hipLaunchKernelGGL((diag_bwd_kernel<K, VEC, R, AINV, QP, kStreamAll, FFM>), g, block, 0, s, args);
+    else
+        hipLaunchKernelGGL((diag_bwd_kernel<K, VEC, R, AINV, QP, QP && !AINV ? kStreamOut : kStreamAll, FFM>), g, block, 0, s,
+                           args);
+}
 template <Kind K, int VEC, int R, bool AINV, bool FFM = false>
 static hipError_t launch_bwd(const DiagBwdArgs& args, int64_t ntiles, hipStream_t s) {
-    const dim3 grid((unsigned)ntiles), block(256);
-    if constexpr (VEC > 1) {
-        if (args.Qp == 8) {
-            hipLaunchKernelGGL((diag_bwd_kernel<K, VEC, R, AINV, 8, FFM>), grid, block, 0, s, args);
-            return hipGetLastError();
-        }
-    }
-    hipLaunchKernelGGL((diag_bwd_kernel<K, VEC, R, AINV, 0, FFM>), grid, block, 0, s, args);
+    bool fixed = false;
+    if constexpr (VEC > 1) fixed = args.Qp == 8;
+    if (fixed) launch_bwd_pol<K, VEC, R, AINV, (VEC > 1 ? 8 : 0), FFM>(args, (unsigned)ntiles, s);
+    else launch_bwd_pol<K, VEC, R, AINV, 0, FFM>(args, (unsigned)ntiles, s);
     return hipGetLastError();
 }
 

@@ -54,11 +54,12 @@ namespace memoroid {
 // QP: the plan's lane-group width when it is fixed at compile time (8, a whole
 // chain row of vector-wide lanes: every vectorised call with at least one line
 // of features), 0 when it comes from the plan.
-template <Kind IN, Kind OUT, int VEC, int R, bool AINV, int QP, bool FFM = false>
+template <Kind IN, Kind OUT, int VEC, int R, bool AINV, int QP, int POL, bool FFM = false>
 __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
     static_assert(!FFM || (IN == K_C64 && OUT == K_C64 && AINV), "FFM: complex state, generated a");
     static_assert(R >= 1 && R <= 32, "a lane's steps are bits of 32-bit masks");
     static_assert(QP == 0 || QP == 8, "fixed group width: whole chain rows");
+    constexpr int kLd = POL == kStreamAll ? kNt : 0, kSt = POL != kCached ? kNt : 0;
     using S = typename StateOf<IN>::type;
     using CIn = Codec<IN, VEC>;
     using COut = Codec<OUT, VEC>;
@@ -206,8 +207,8 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
     } else {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            raw_bload(rx[r], rs_x, in_off + r * in_step);
-            if constexpr (!AINV) raw_bload(ra[r], rs_a, in_off + r * in_step);
+            raw_bload<kLd>(rx[r], rs_x, in_off + r * in_step);
+            if constexpr (!AINV) raw_bload<kLd>(ra[r], rs_a, in_off + r * in_step);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
             replay(r);
             RawVec<OUT, VEC> o1;
             COut::put_all(o1, hv);
-            raw_bstore_nt(rs_h, out_off + r * out_step, o1);
+            raw_bstore<kSt>(rs_h, out_off + r * out_step, o1);
         }
     } else {
         // all outputs are computed before any store (in the registers that
@@ -451,33 +452,38 @@ __global__ __launch_bounds__(256) void diag_fwd_kernel(DiagFwdArgs p) {
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if constexpr (kInPlace) raw_bstore_nt(rs_h, out_off + r * out_step, rx[r]);
-            else raw_bstore_nt(rs_h, out_off + r * out_step, o[r]);
+            if constexpr (kInPlace) raw_bstore<kSt>(rs_h, out_off + r * out_step, rx[r]);
+            else raw_bstore<kSt>(rs_h, out_off + r * out_step, o[r]);
         }
     }
 }
 
 // ------------------------------------------------------------------ launch
 
+template <Kind IN, Kind OUT, int VEC, int R, bool AINV, int QP, bool FFM>
+static void launch_fwd_pol(const DiagFwdArgs& args, unsigned grid, hipStream_t s) {
+    const dim3 g(grid), block(256);
+    if (args.policy == kCached)
+        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, AINV, QP, kCached, FFM>), g, block, 0, s, args);
+    else if (QP == 0 || args.policy == kStreamAll)     // no kStreamOut for the rarer plans
+        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, AINV, QP, kStreamAll, FFM>), g, block, 0, s, args);
+    else
+        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, AINV, QP, QP ? kStreamOut : kStreamAll, FFM>), g, block, 0,
+                           s, args);
+}
+template <Kind IN, Kind OUT, int VEC, int R, bool AINV, bool FFM = false>
+static void launch_fwd_qp(const DiagFwdArgs& args, unsigned grid, hipStream_t s) {
+    if constexpr (VEC > 1) {
+        if (args.Qp == 8) return launch_fwd_pol<IN, OUT, VEC, R, AINV, 8, FFM>(args, grid, s);
+    }
+    launch_fwd_pol<IN, OUT, VEC, R, AINV, 0, FFM>(args, grid, s);
+}
 // R: steps per lane with a time-invariant a; RS with a per-step a (the host
 // plans the tiles with the same counts, diag_fwd_rows)
-template <Kind IN, Kind OUT, int VEC, int R, int RS, int QP>
-static void launch_fwd_qp(const DiagFwdArgs& args, int64_t ntiles, bool ainv, hipStream_t s) {
-    if (ainv)
-        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, true, QP>), dim3((unsigned)ntiles), dim3(256), 0, s, args);
-    else
-        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, RS, false, QP>), dim3((unsigned)ntiles), dim3(256), 0, s,
-                           args);
-}
 template <Kind IN, Kind OUT, int VEC, int R, int RS = R>
 static hipError_t launch_fwd(const DiagFwdArgs& args, int64_t ntiles, bool ainv, hipStream_t s) {
-    if constexpr (VEC > 1) {
-        if (args.Qp == 8) {
-            launch_fwd_qp<IN, OUT, VEC, R, RS, 8>(args, ntiles, ainv, s);
-            return hipGetLastError();
-        }
-    }
-    launch_fwd_qp<IN, OUT, VEC, R, RS, 0>(args, ntiles, ainv, s);
+    if (ainv) launch_fwd_qp<IN, OUT, VEC, R, true>(args, (unsigned)ntiles, s);
+    else launch_fwd_qp<IN, OUT, VEC, RS, false>(args, (unsigned)ntiles, s);
     return hipGetLastError();
 }
 
@@ -486,16 +492,9 @@ hipError_t ffm_fwd_launch(bool vec, const DiagFwdArgs& args, int64_t ntiles, hip
     constexpr int VC = KindInfo<K_C64>::vec;
     (void)ntiles;
     // whole groups of kXcds positions per chain (see the kernel)
-    const int64_t grid = ((args.nt + kXcds - 1) / kXcds) * kXcds * args.nchains;
-    if (vec && args.Qp == 8)
-        hipLaunchKernelGGL((diag_fwd_kernel<K_C64, K_C64, VC, R, true, 8, true>), dim3((unsigned)grid), dim3(256), 0, s,
-                           args);
-    else if (vec)
-        hipLaunchKernelGGL((diag_fwd_kernel<K_C64, K_C64, VC, R, true, 0, true>), dim3((unsigned)grid), dim3(256), 0, s,
-                           args);
-    else
-        hipLaunchKernelGGL((diag_fwd_kernel<K_C64, K_C64, 1, R, true, 0, true>), dim3((unsigned)grid), dim3(256), 0, s,
-                           args);
+    const unsigned grid = (unsigned)(((args.nt + kXcds - 1) / kXcds) * kXcds * args.nchains);
+    if (vec) launch_fwd_qp<K_C64, K_C64, VC, R, true, true>(args, grid, s);
+    else launch_fwd_qp<K_C64, K_C64, 1, R, true, true>(args, grid, s);
     return hipGetLastError();
 }
 

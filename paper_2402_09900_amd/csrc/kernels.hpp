@@ -77,6 +77,25 @@ constexpr int kFfmBwdRows = MEMOROID_FFM_BWD_ROWS;
 #endif
 constexpr int kFfmFwdRows = MEMOROID_FFM_FWD_ROWS;
 
+// Cache policy of a diagonal scan's tensors (us, forward / reverse, T x d with
+// a per step unless noted):
+//   kCached: feature rows that are not whole 128-byte lines.  A line then holds
+//     features of two chains (or two rows), and a non-temporal access drops or
+//     writes it once for each: f32 8 x 30000 x 51 67 / 129 -> 43 / 70, complex
+//     105 / 143 -> 55 / 97 with an invariant a, f32 65536 x 100 34 / 68 -> 26 / 43.
+//   kStreamOut: whole lines, inputs up to kCachedInputBytes.  Outputs go past
+//     the caches and inputs through them, so that what the 256 MB Infinity
+//     Cache holds of an input is found there: forward and reverse with a per
+//     step, T = 16384, 32768, 65536 x 256, f32 39 / 67 / 115 -> 36 / 58 / 101
+//     with the same buffers each time; with buffers that no cache holds 39.4 /
+//     67.7 / 115.5 -> 38.9 / 67.6 / 113.6.
+//   kStreamAll: larger inputs (f32 2^18 x 256 387 against 389 with cached
+//     loads, complex 720 against 734), and the reverse scan with an invariant
+//     a, which cached loads slow by 3 % at every size when no cache holds its
+//     inputs (forward and reverse, f32 16384 x 256 27.2 -> 28.8, complex 65536
+//     x 256 132 -> 135).
+enum CachePolicy { kCached = 0, kStreamOut = 1, kStreamAll = 2 };
+constexpr int64_t kCachedInputBytes = (int64_t)320 << 20;
 
 struct DiagFwdArgs {
     const void* a;
@@ -88,7 +107,7 @@ struct DiagFwdArgs {
     int32_t Qp;        // lanes per step row of a tile (power of two, <= 64)
     int32_t nfb;       // feature blocks per tape
     int32_t nchains;   // tapes * feature blocks
-    int32_t pad0;
+    int32_t policy;    // a CachePolicy
     int64_t nt;        // tiles per chain
     // descriptor words, bank 0 (bank 1 lies `bank` bytes further on)
     void* agg;         // [tiles][Dp] aggregate descriptor words
@@ -124,7 +143,7 @@ struct DiagBwdArgs {
     int32_t Qp;
     int32_t nfb;
     int32_t nchains;
-    int32_t pad0;
+    int32_t policy;
     void* agg;         // bank 0, as in DiagFwdArgs
     void* incl;
     int64_t bank;

@@ -84,10 +84,9 @@ template <Kind K, int VEC> struct RawVec {
 // Raw buffer loads and stores: 32-bit byte offsets from a base held in
 // scalar registers, with the range check done by the memory pipeline -- a
 // load at or past the resource's byte count returns zeros and a store there
-// is dropped -- so the edges of a tile need no branches or masks.  Both use
-// the non-temporal cache policy: the scans read and write every element
-// once (non-temporal loads took the f32 T = 2^20, d = 256 forward / reverse
-// scans from 575 / 946 to 562 / 935 us).  Every offset goes in the per-lane
+// is dropped -- so the edges of a tile need no branches or masks.  The scans
+// read and write every element once, but non-temporal access is not always
+// best: see CachePolicy in kernels.hpp.  Every offset goes in the per-lane
 // (range-checked) operand; the scalar offset, which the check does not
 // cover, is always 0.
 typedef __amdgpu_buffer_rsrc_t Rsrc;
@@ -107,11 +106,11 @@ __device__ __forceinline__ uint32_t bload_u8(Rsrc r, uint32_t off) {
 template <int BYTES> struct WideAccess;
 
 template <> struct WideAccess<2> {
-    template <int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
-        w[0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, kNt);
+    template <int AUX, int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
+        w[0] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)off, 0, AUX);
     }
-    template <int W> __device__ static void bstore_nt(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
-        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)w[0], r, (int)off, 0, kNt);
+    template <int AUX, int W> __device__ static void bstore(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
+        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)w[0], r, (int)off, 0, AUX);
     }
     template <int W> __device__ static void load(uint32_t (&w)[W], const void* p) {
         w[0] = *(const uint16_t*)p;
@@ -121,11 +120,11 @@ template <> struct WideAccess<2> {
     }
 };
 template <> struct WideAccess<4> {
-    template <int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
-        w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, kNt);
+    template <int AUX, int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
+        w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX);
     }
-    template <int W> __device__ static void bstore_nt(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
-        __builtin_amdgcn_raw_buffer_store_b32(w[0], r, (int)off, 0, kNt);
+    template <int AUX, int W> __device__ static void bstore(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
+        __builtin_amdgcn_raw_buffer_store_b32(w[0], r, (int)off, 0, AUX);
     }
     template <int W> __device__ static void load(uint32_t (&w)[W], const void* p) {
         w[0] = *(const uint32_t*)p;
@@ -135,13 +134,13 @@ template <> struct WideAccess<4> {
     }
 };
 template <> struct WideAccess<8> {
-    template <int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, kNt);
+    template <int AUX, int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, AUX);
         w[0] = v.x; w[1] = v.y;
     }
-    template <int W> __device__ static void bstore_nt(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
+    template <int AUX, int W> __device__ static void bstore(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
         const u32x2 v = {w[0], w[1]};
-        __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, kNt);
+        __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, AUX);
     }
     template <int W> __device__ static void load(uint32_t (&w)[W], const void* p) {
         u32x2 v = *(const u32x2*)p;
@@ -153,13 +152,13 @@ template <> struct WideAccess<8> {
     }
 };
 template <> struct WideAccess<16> {
-    template <int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kNt);
+    template <int AUX, int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
+        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX);
         w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
     }
-    template <int W> __device__ static void bstore_nt(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
+    template <int AUX, int W> __device__ static void bstore(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
         const u32x4 v = {w[0], w[1], w[2], w[3]};
-        __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, kNt);
+        __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, AUX);
     }
     template <int W> __device__ static void load(uint32_t (&w)[W], const void* p) {
         u32x4 v = *(const u32x4*)p;
@@ -171,17 +170,17 @@ template <> struct WideAccess<16> {
     }
 };
 template <> struct WideAccess<32> {
-    template <int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
-        const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, kNt);
-        const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + 16u), 0, kNt);
+    template <int AUX, int W> __device__ static void bload(uint32_t (&w)[W], Rsrc r, uint32_t off) {
+        const u32x4 v0 = __builtin_amdgcn_raw_buffer_load_b128(r, (int)off, 0, AUX);
+        const u32x4 v1 = __builtin_amdgcn_raw_buffer_load_b128(r, (int)(off + 16u), 0, AUX);
         w[0] = v0.x; w[1] = v0.y; w[2] = v0.z; w[3] = v0.w;
         w[4] = v1.x; w[5] = v1.y; w[6] = v1.z; w[7] = v1.w;
     }
-    template <int W> __device__ static void bstore_nt(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
+    template <int AUX, int W> __device__ static void bstore(Rsrc r, uint32_t off, const uint32_t (&w)[W]) {
         const u32x4 v0 = {w[0], w[1], w[2], w[3]};
         const u32x4 v1 = {w[4], w[5], w[6], w[7]};
-        __builtin_amdgcn_raw_buffer_store_b128(v0, r, (int)off, 0, kNt);
-        __builtin_amdgcn_raw_buffer_store_b128(v1, r, (int)(off + 16u), 0, kNt);
+        __builtin_amdgcn_raw_buffer_store_b128(v0, r, (int)off, 0, AUX);
+        __builtin_amdgcn_raw_buffer_store_b128(v1, r, (int)(off + 16u), 0, AUX);
     }
     template <int W> __device__ static void load(uint32_t (&w)[W], const void* p) {
         u32x4 v0 = ((const u32x4*)p)[0];
@@ -207,14 +206,14 @@ __device__ __forceinline__ void raw_store_nt(void* p, const RawVec<K, VEC>& r) {
     WideAccess<RawVec<K, VEC>::BYTES>::store_nt(p, r.w);
 }
 
-template <Kind K, int VEC>
+template <int AUX, Kind K, int VEC>
 __device__ __forceinline__ void raw_bload(RawVec<K, VEC>& r, Rsrc rs, uint32_t off) {
-    WideAccess<RawVec<K, VEC>::BYTES>::bload(r.w, rs, off);
+    WideAccess<RawVec<K, VEC>::BYTES>::template bload<AUX>(r.w, rs, off);
 }
 
-template <Kind K, int VEC>
-__device__ __forceinline__ void raw_bstore_nt(Rsrc rs, uint32_t off, const RawVec<K, VEC>& r) {
-    WideAccess<RawVec<K, VEC>::BYTES>::bstore_nt(rs, off, r.w);
+template <int AUX, Kind K, int VEC>
+__device__ __forceinline__ void raw_bstore(Rsrc rs, uint32_t off, const RawVec<K, VEC>& r) {
+    WideAccess<RawVec<K, VEC>::BYTES>::template bstore<AUX>(rs, off, r.w);
 }
 
 // decode element i of a raw vector into its state type

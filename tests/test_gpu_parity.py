@@ -318,6 +318,18 @@ def test_tile_boundary_lengths(dtype, inv, d):
             check_bwd(w, label="tile edge L=%s" % Ls)
 
 
+# whole chains of vector-wide lanes on rows that are not whole 128-byte lines
+# (cached access), and the same rows one line wide or more (outputs streamed)
+@pytest.mark.parametrize("inv", [False, True])
+@pytest.mark.parametrize("dtype,d", [("f32", 100), ("f32", 96), ("c64", 50), ("c64", 48), ("bf16", 72), ("bf16", 128)])
+def test_cache_policies_at_tile_edges(dtype, d, inv):
+    for T in (_tile_lengths(dtype, inv, d)[-1] + 1, 2 * _tile_lengths(dtype, inv, d)[0] - 1):
+        w = tapes.make_custom_diag(dtype, 2, T, d, inv, seed=5000 + T + d, mean_episode=90.0)
+        check_fwd(w, label="cache policy")
+        if dtype != "bf16":
+            check_bwd(w, label="cache policy")
+
+
 @pytest.mark.parametrize("dtype,inv", [(dt, inv) for dt in ("f32", "bf16", "c64") for inv in (False, True)])
 def test_flags_at_word_and_lane_edges(dtype, inv):
     """Full-width rows read a wavefront's begin flags as 64-bit words: begins
