@@ -21,6 +21,7 @@ there is no fallback implementation.
 """
 from __future__ import annotations
 
+import collections
 import ctypes
 import os
 from typing import Optional, Tuple
@@ -373,42 +374,56 @@ def _workspace(nbytes: int, device, workspace=None):
     return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
 
 
-_PREPARED = None            # OrderedDict: key -> (workspace tensor, its pointer, its size, entry point)
+class _Workspace:
+    """A call's workspace (the tensor with its pointer and size), entry point
+    and stream.  The caller holds it until its C call has returned, so that no
+    other thread's call can free the memory before the kernel is launched."""
+
+    __slots__ = ("tensor", "pointer", "size", "fn", "stream")
+
+    def __init__(self, tensor, fn, stream):
+        self.tensor = tensor
+        self.pointer = tensor.data_ptr()
+        self.size = tensor.numel()
+        self.fn = fn
+        self.stream = stream
+
+
+_PREPARED = collections.OrderedDict()           # key -> _Workspace
 _PREPARED_MAX = 32
 
 
 def _prepared(nbytes, device, key, pointers, workspace, entry):
-    """A call's workspace (pointer and size), its entry point and its stream.
-    With no workspace given: a prepared workspace from the cache and the
-    `entry`_prepared function.  `key` names the entry point and the sizes and
-    flags its layout depends on (so also its size, nbytes()); whether every
-    operand is 16-byte aligned (which selects the vectorised kernels) is added
-    here, from the operands' pointers or'ed together.  A workspace given by
-    the caller goes to the self-initialising `entry` (a smaller one raises
-    EWORKSPACE there)."""
-    global _PREPARED
+    """The _Workspace of a call.  With no workspace given: a prepared one
+    from the cache and the `entry`_prepared function.  `key` names the entry
+    point and the sizes and flags its layout depends on (so also its size,
+    nbytes()); whether every operand is 16-byte aligned (which selects the
+    vectorised kernels) is added here, from the operands' pointers or'ed
+    together.  A workspace given by the caller goes to the self-initialising
+    `entry` (a smaller one raises EWORKSPACE there)."""
     stream = _raw_stream(device.index)
     if workspace is not None:
-        return workspace.data_ptr(), workspace.numel(), getattr(lib(), entry), stream
+        return _Workspace(workspace, getattr(lib(), entry), stream)
     full = (device.index, stream, pointers % 16 == 0, key)
-    if _PREPARED is None:
-        import collections
-        _PREPARED = collections.OrderedDict()
     got = _PREPARED.get(full)
     if got is None:
         torch = _torch()
-        ws = torch.empty(max(nbytes(), 256), dtype=torch.uint8, device=device)
-        got = (ws, ws.data_ptr(), ws.numel(), getattr(lib(), entry + "_prepared"))
-        _raise(lib().memoroid_workspace_prepare(got[1], got[2], stream), "memoroid_workspace_prepare")
-        _PREPARED[full] = got
+        tensor = torch.empty(max(nbytes(), 256), dtype=torch.uint8, device=device)
+        got = _Workspace(tensor, getattr(lib(), entry + "_prepared"), stream)
+        _raise(lib().memoroid_workspace_prepare(got.pointer, got.size, stream), "memoroid_workspace_prepare")
+        # of two threads that both found nothing, the second takes the first's
+        got = _PREPARED.setdefault(full, got)
         while len(_PREPARED) > _PREPARED_MAX:
-            _PREPARED.popitem(last=False)
+            try:
+                _PREPARED.popitem(last=False)
+            except KeyError:            # emptied by other threads meanwhile
+                break
     else:
         try:
             _PREPARED.move_to_end(full)
         except KeyError:                # dropped by another thread's call meanwhile
-            _PREPARED[full] = got
-    return got[1], got[2], got[3], stream
+            pass
+    return got
 
 
 def _diag_shapes(a, x, start):
@@ -448,11 +463,11 @@ def scan_diag(a, x, start, out_dtype=None, episode_idx: bool = False, workspace=
     h = torch.empty((B, T, d), dtype=out_torch, device=dev)
     idx = torch.empty((B, T), dtype=torch.int32, device=dev) if episode_idx else None
     ap, xp, hp = a.data_ptr(), x.data_ptr(), h.data_ptr()
-    ws, size, fn, stream = _prepared(lambda: lib().memoroid_scan_diag_workspace_bytes(B, T, d, in_dt, out_dt), dev,
-                                     ("diag", B, T, d, in_dt, out_dt, stride), ap | xp | hp, workspace,
-                                     "memoroid_scan_diag")
-    st = fn(ap, stride, xp, start.data_ptr(), hp, None if idx is None else idx.data_ptr(), B, T, d, in_dt, out_dt,
-            ws, size, stream)
+    ws = _prepared(lambda: lib().memoroid_scan_diag_workspace_bytes(B, T, d, in_dt, out_dt), dev,
+                   ("diag", B, T, d, in_dt, out_dt, stride), ap | xp | hp, workspace,
+                   "memoroid_scan_diag")
+    st = ws.fn(ap, stride, xp, start.data_ptr(), hp, None if idx is None else idx.data_ptr(), B, T, d, in_dt, out_dt,
+               ws.pointer, ws.size, ws.stream)
     if st:
         _raise(st, "memoroid_scan_diag")
     return (h, idx) if episode_idx else h
@@ -480,10 +495,10 @@ def scan_diag_bwd(a, start, h, grad_h, need_grad_a: bool = True, workspace=None)
     ap, gp, xp = a.data_ptr(), grad_h.data_ptr(), gx.data_ptr()
     hp = 0 if h is None else h.data_ptr()
     dp = 0 if ga is None else ga.data_ptr()
-    ws, size, fn, stream = _prepared(lambda: lib().memoroid_scan_diag_bwd_workspace_bytes(B, T, d, dt, stride), dev,
-                                     ("diag_bwd", B, T, d, dt, stride, need_grad_a), ap | gp | xp | hp | dp, workspace,
-                                     "memoroid_scan_diag_bwd")
-    st = fn(ap, stride, start.data_ptr(), hp, gp, xp, dp, B, T, d, dt, ws, size, stream)
+    ws = _prepared(lambda: lib().memoroid_scan_diag_bwd_workspace_bytes(B, T, d, dt, stride), dev,
+                   ("diag_bwd", B, T, d, dt, stride, need_grad_a), ap | gp | xp | hp | dp, workspace,
+                   "memoroid_scan_diag_bwd")
+    st = ws.fn(ap, stride, start.data_ptr(), hp, gp, xp, dp, B, T, d, dt, ws.pointer, ws.size, ws.stream)
     if st:
         _raise(st, "memoroid_scan_diag_bwd")
     return gx, ga
@@ -535,10 +550,10 @@ def scan_ffm(alpha, omega, x, start, episode_idx: bool = False, workspace=None):
         raise TypeError("start must be uint8")
     S = torch.empty((B, T, m, c), dtype=torch.complex64, device=dev)
     idx = torch.empty((B, T), dtype=torch.int32, device=dev) if episode_idx else None
-    ws, size, fn, stream = _prepared(lambda: lib().memoroid_scan_ffm_workspace_bytes(B, T, m, c), dev,
-                                     ("ffm", B, T, m, c), S.data_ptr(), workspace, "memoroid_scan_ffm")
-    st = fn(alpha.data_ptr(), omega.data_ptr(), x.data_ptr(), start.data_ptr(), S.data_ptr(),
-            idx.data_ptr() if idx is not None else None, B, T, m, c, ws, size, stream)
+    ws = _prepared(lambda: lib().memoroid_scan_ffm_workspace_bytes(B, T, m, c), dev,
+                   ("ffm", B, T, m, c), S.data_ptr(), workspace, "memoroid_scan_ffm")
+    st = ws.fn(alpha.data_ptr(), omega.data_ptr(), x.data_ptr(), start.data_ptr(), S.data_ptr(),
+               idx.data_ptr() if idx is not None else None, B, T, m, c, ws.pointer, ws.size, ws.stream)
     _raise(st, "memoroid_scan_ffm")
     if squeeze:
         S = S[0]
@@ -557,9 +572,9 @@ def tbb_begin_indices(start, offset: int = 0, workspace=None):
     n = start.numel()
     idx = torch.empty(max(n, 1), dtype=torch.int64, device=dev)
     count = torch.empty(1, dtype=torch.int64, device=dev)
-    ws, size, fn, stream = _prepared(lambda: lib().memoroid_tbb_begin_indices_workspace_bytes(n), dev,
-                                     ("tbb_begins", n), 0, workspace, "memoroid_tbb_begin_indices")
-    st = fn(start.data_ptr(), n, int(offset), idx.data_ptr(), count.data_ptr(), ws, size, stream)
+    ws = _prepared(lambda: lib().memoroid_tbb_begin_indices_workspace_bytes(n), dev,
+                   ("tbb_begins", n), 0, workspace, "memoroid_tbb_begin_indices")
+    st = ws.fn(start.data_ptr(), n, int(offset), idx.data_ptr(), count.data_ptr(), ws.pointer, ws.size, ws.stream)
     _raise(st, "memoroid_tbb_begin_indices")
     return idx, count
 
@@ -579,10 +594,10 @@ def tbb_sample(D, I, draws, batch: int, workspace=None):
     out_src = torch.empty(batch, dtype=torch.int64, device=dev)
     filled = torch.empty(1, dtype=torch.int64, device=dev)
     nd = draws.numel()
-    ws, size, fn, stream = _prepared(lambda: lib().memoroid_tbb_sample_workspace_bytes(nd, batch), dev,
-                                     ("tbb_sample", nd, batch), 0, workspace, "memoroid_tbb_sample")
-    st = fn(D.data_ptr(), n_D, row_bytes, I.data_ptr(), I.numel(), draws.data_ptr(), nd, batch, out.data_ptr(),
-            out_start.data_ptr(), out_src.data_ptr(), filled.data_ptr(), ws, size, stream)
+    ws = _prepared(lambda: lib().memoroid_tbb_sample_workspace_bytes(nd, batch), dev,
+                   ("tbb_sample", nd, batch), 0, workspace, "memoroid_tbb_sample")
+    st = ws.fn(D.data_ptr(), n_D, row_bytes, I.data_ptr(), I.numel(), draws.data_ptr(), nd, batch, out.data_ptr(),
+               out_start.data_ptr(), out_src.data_ptr(), filled.data_ptr(), ws.pointer, ws.size, ws.stream)
     _raise(st, "memoroid_tbb_sample")
     return out, out_start, out_src, filled
 
@@ -604,11 +619,11 @@ def scan_ffm_bwd(alpha, omega, start, S, grad_S, params: bool = True, workspace=
     ga = torch.empty(m, dtype=torch.float32, device=dev) if params else None
     gw = torch.empty(c, dtype=torch.float32, device=dev) if params else None
     sp, gp = 0 if S is None else S.data_ptr(), grad_S.data_ptr()
-    ws, size, fn, stream = _prepared(lambda: lib().memoroid_scan_ffm_bwd_workspace_bytes(B, T, m, c), dev,
-                                     ("ffm_bwd", B, T, m, c, params), sp | gp, workspace, "memoroid_scan_ffm_bwd")
-    st = fn(alpha.data_ptr(), omega.data_ptr(), start.data_ptr(), sp, gp, gx.data_ptr(),
-            ga.data_ptr() if ga is not None else None, gw.data_ptr() if gw is not None else None, B, T, m, c, ws, size,
-            stream)
+    ws = _prepared(lambda: lib().memoroid_scan_ffm_bwd_workspace_bytes(B, T, m, c), dev,
+                   ("ffm_bwd", B, T, m, c, params), sp | gp, workspace, "memoroid_scan_ffm_bwd")
+    st = ws.fn(alpha.data_ptr(), omega.data_ptr(), start.data_ptr(), sp, gp, gx.data_ptr(),
+               ga.data_ptr() if ga is not None else None, gw.data_ptr() if gw is not None else None, B, T, m, c,
+               ws.pointer, ws.size, ws.stream)
     _raise(st, "memoroid_scan_ffm_bwd")
     return (gx[0] if squeeze else gx), ga, gw
 
@@ -633,9 +648,9 @@ def discounted_return(r, start, gamma: float, workspace=None):
     if r.dtype != torch.float32 or start.dtype != torch.uint8:
         raise TypeError("r must be float32 and start uint8")
     G = torch.empty((B, T), dtype=torch.float32, device=dev)
-    ws, size, fn, stream = _prepared(lambda: lib().memoroid_discount_workspace_bytes(B, T), dev, ("return", B, T), 0,
-                                     workspace, "memoroid_discounted_return")
-    st = fn(r.data_ptr(), start.data_ptr(), float(gamma), G.data_ptr(), B, T, ws, size, stream)
+    ws = _prepared(lambda: lib().memoroid_discount_workspace_bytes(B, T), dev, ("return", B, T), 0,
+                   workspace, "memoroid_discounted_return")
+    st = ws.fn(r.data_ptr(), start.data_ptr(), float(gamma), G.data_ptr(), B, T, ws.pointer, ws.size, ws.stream)
     if st:
         _raise(st, "memoroid_discounted_return")
     return _shaped(G, *shape)
@@ -658,11 +673,11 @@ def gae(r, value, start, gamma: float, lam: float, value_next=None, done=None, t
             raise TypeError("start and done must be uint8")
     adv = torch.empty((B, T), dtype=torch.float32, device=dev)
     tg = torch.empty((B, T), dtype=torch.float32, device=dev) if target else None
-    ws, size, fn, stream = _prepared(lambda: lib().memoroid_discount_workspace_bytes(B, T), dev, ("gae", B, T), 0,
-                                     workspace, "memoroid_gae")
-    st = fn(r.data_ptr(), value.data_ptr(), value_next.data_ptr() if value_next is not None else None,
-            done.data_ptr() if done is not None else None, start.data_ptr(), float(gamma), float(lam), adv.data_ptr(),
-            tg.data_ptr() if tg is not None else None, B, T, ws, size, stream)
+    ws = _prepared(lambda: lib().memoroid_discount_workspace_bytes(B, T), dev, ("gae", B, T), 0,
+                   workspace, "memoroid_gae")
+    st = ws.fn(r.data_ptr(), value.data_ptr(), value_next.data_ptr() if value_next is not None else None,
+               done.data_ptr() if done is not None else None, start.data_ptr(), float(gamma), float(lam),
+               adv.data_ptr(), tg.data_ptr() if tg is not None else None, B, T, ws.pointer, ws.size, ws.stream)
     if st:
         _raise(st, "memoroid_gae")
     return _shaped(adv, *shape), (_shaped(tg, *shape) if tg is not None else None)
