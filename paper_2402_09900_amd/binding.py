@@ -24,6 +24,7 @@ from __future__ import annotations
 import collections
 import ctypes
 import os
+import threading
 from typing import Optional, Tuple
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -377,9 +378,12 @@ def _workspace(nbytes: int, device, workspace=None):
 class _Workspace:
     """A call's workspace (the tensor with its pointer and size), entry point
     and stream.  The caller holds it until its C call has returned, so that no
-    other thread's call can free the memory before the kernel is launched."""
+    other thread's call can free the memory before the kernel is launched, and
+    makes that call under `lock`: a call may launch several kernels that hand
+    values on in the workspace (TBB sampling, the FFM gradient), and another
+    thread's on the same stream must not come between them."""
 
-    __slots__ = ("tensor", "pointer", "size", "fn", "stream")
+    __slots__ = ("tensor", "pointer", "size", "fn", "stream", "lock")
 
     def __init__(self, tensor, fn, stream):
         self.tensor = tensor
@@ -387,6 +391,7 @@ class _Workspace:
         self.size = tensor.numel()
         self.fn = fn
         self.stream = stream
+        self.lock = threading.RLock()
 
 
 _PREPARED = collections.OrderedDict()           # key -> _Workspace
@@ -466,8 +471,9 @@ def scan_diag(a, x, start, out_dtype=None, episode_idx: bool = False, workspace=
     ws = _prepared(lambda: lib().memoroid_scan_diag_workspace_bytes(B, T, d, in_dt, out_dt), dev,
                    ("diag", B, T, d, in_dt, out_dt, stride), ap | xp | hp, workspace,
                    "memoroid_scan_diag")
-    st = ws.fn(ap, stride, xp, start.data_ptr(), hp, None if idx is None else idx.data_ptr(), B, T, d, in_dt, out_dt,
-               ws.pointer, ws.size, ws.stream)
+    with ws.lock:
+        st = ws.fn(ap, stride, xp, start.data_ptr(), hp, None if idx is None else idx.data_ptr(), B, T, d, in_dt,
+                   out_dt, ws.pointer, ws.size, ws.stream)
     if st:
         _raise(st, "memoroid_scan_diag")
     return (h, idx) if episode_idx else h
@@ -498,7 +504,8 @@ def scan_diag_bwd(a, start, h, grad_h, need_grad_a: bool = True, workspace=None)
     ws = _prepared(lambda: lib().memoroid_scan_diag_bwd_workspace_bytes(B, T, d, dt, stride), dev,
                    ("diag_bwd", B, T, d, dt, stride, need_grad_a), ap | gp | xp | hp | dp, workspace,
                    "memoroid_scan_diag_bwd")
-    st = ws.fn(ap, stride, start.data_ptr(), hp, gp, xp, dp, B, T, d, dt, ws.pointer, ws.size, ws.stream)
+    with ws.lock:
+        st = ws.fn(ap, stride, start.data_ptr(), hp, gp, xp, dp, B, T, d, dt, ws.pointer, ws.size, ws.stream)
     if st:
         _raise(st, "memoroid_scan_diag_bwd")
     return gx, ga
@@ -552,8 +559,9 @@ def scan_ffm(alpha, omega, x, start, episode_idx: bool = False, workspace=None):
     idx = torch.empty((B, T), dtype=torch.int32, device=dev) if episode_idx else None
     ws = _prepared(lambda: lib().memoroid_scan_ffm_workspace_bytes(B, T, m, c), dev,
                    ("ffm", B, T, m, c), S.data_ptr(), workspace, "memoroid_scan_ffm")
-    st = ws.fn(alpha.data_ptr(), omega.data_ptr(), x.data_ptr(), start.data_ptr(), S.data_ptr(),
-               idx.data_ptr() if idx is not None else None, B, T, m, c, ws.pointer, ws.size, ws.stream)
+    with ws.lock:
+        st = ws.fn(alpha.data_ptr(), omega.data_ptr(), x.data_ptr(), start.data_ptr(), S.data_ptr(),
+                   idx.data_ptr() if idx is not None else None, B, T, m, c, ws.pointer, ws.size, ws.stream)
     _raise(st, "memoroid_scan_ffm")
     if squeeze:
         S = S[0]
@@ -574,7 +582,8 @@ def tbb_begin_indices(start, offset: int = 0, workspace=None):
     count = torch.empty(1, dtype=torch.int64, device=dev)
     ws = _prepared(lambda: lib().memoroid_tbb_begin_indices_workspace_bytes(n), dev,
                    ("tbb_begins", n), 0, workspace, "memoroid_tbb_begin_indices")
-    st = ws.fn(start.data_ptr(), n, int(offset), idx.data_ptr(), count.data_ptr(), ws.pointer, ws.size, ws.stream)
+    with ws.lock:
+        st = ws.fn(start.data_ptr(), n, int(offset), idx.data_ptr(), count.data_ptr(), ws.pointer, ws.size, ws.stream)
     _raise(st, "memoroid_tbb_begin_indices")
     return idx, count
 
@@ -596,8 +605,9 @@ def tbb_sample(D, I, draws, batch: int, workspace=None):
     nd = draws.numel()
     ws = _prepared(lambda: lib().memoroid_tbb_sample_workspace_bytes(nd, batch), dev,
                    ("tbb_sample", nd, batch), 0, workspace, "memoroid_tbb_sample")
-    st = ws.fn(D.data_ptr(), n_D, row_bytes, I.data_ptr(), I.numel(), draws.data_ptr(), nd, batch, out.data_ptr(),
-               out_start.data_ptr(), out_src.data_ptr(), filled.data_ptr(), ws.pointer, ws.size, ws.stream)
+    with ws.lock:
+        st = ws.fn(D.data_ptr(), n_D, row_bytes, I.data_ptr(), I.numel(), draws.data_ptr(), nd, batch, out.data_ptr(),
+                   out_start.data_ptr(), out_src.data_ptr(), filled.data_ptr(), ws.pointer, ws.size, ws.stream)
     _raise(st, "memoroid_tbb_sample")
     return out, out_start, out_src, filled
 
@@ -621,9 +631,10 @@ def scan_ffm_bwd(alpha, omega, start, S, grad_S, params: bool = True, workspace=
     sp, gp = 0 if S is None else S.data_ptr(), grad_S.data_ptr()
     ws = _prepared(lambda: lib().memoroid_scan_ffm_bwd_workspace_bytes(B, T, m, c), dev,
                    ("ffm_bwd", B, T, m, c, params), sp | gp, workspace, "memoroid_scan_ffm_bwd")
-    st = ws.fn(alpha.data_ptr(), omega.data_ptr(), start.data_ptr(), sp, gp, gx.data_ptr(),
-               ga.data_ptr() if ga is not None else None, gw.data_ptr() if gw is not None else None, B, T, m, c,
-               ws.pointer, ws.size, ws.stream)
+    with ws.lock:
+        st = ws.fn(alpha.data_ptr(), omega.data_ptr(), start.data_ptr(), sp, gp, gx.data_ptr(),
+                   ga.data_ptr() if ga is not None else None, gw.data_ptr() if gw is not None else None, B, T, m, c,
+                   ws.pointer, ws.size, ws.stream)
     _raise(st, "memoroid_scan_ffm_bwd")
     return (gx[0] if squeeze else gx), ga, gw
 
@@ -650,7 +661,8 @@ def discounted_return(r, start, gamma: float, workspace=None):
     G = torch.empty((B, T), dtype=torch.float32, device=dev)
     ws = _prepared(lambda: lib().memoroid_discount_workspace_bytes(B, T), dev, ("return", B, T), 0,
                    workspace, "memoroid_discounted_return")
-    st = ws.fn(r.data_ptr(), start.data_ptr(), float(gamma), G.data_ptr(), B, T, ws.pointer, ws.size, ws.stream)
+    with ws.lock:
+        st = ws.fn(r.data_ptr(), start.data_ptr(), float(gamma), G.data_ptr(), B, T, ws.pointer, ws.size, ws.stream)
     if st:
         _raise(st, "memoroid_discounted_return")
     return _shaped(G, *shape)
@@ -675,9 +687,10 @@ def gae(r, value, start, gamma: float, lam: float, value_next=None, done=None, t
     tg = torch.empty((B, T), dtype=torch.float32, device=dev) if target else None
     ws = _prepared(lambda: lib().memoroid_discount_workspace_bytes(B, T), dev, ("gae", B, T), 0,
                    workspace, "memoroid_gae")
-    st = ws.fn(r.data_ptr(), value.data_ptr(), value_next.data_ptr() if value_next is not None else None,
-               done.data_ptr() if done is not None else None, start.data_ptr(), float(gamma), float(lam),
-               adv.data_ptr(), tg.data_ptr() if tg is not None else None, B, T, ws.pointer, ws.size, ws.stream)
+    with ws.lock:
+        st = ws.fn(r.data_ptr(), value.data_ptr(), value_next.data_ptr() if value_next is not None else None,
+                   done.data_ptr() if done is not None else None, start.data_ptr(), float(gamma), float(lam),
+                   adv.data_ptr(), tg.data_ptr() if tg is not None else None, B, T, ws.pointer, ws.size, ws.stream)
     if st:
         _raise(st, "memoroid_gae")
     return _shaped(adv, *shape), (_shaped(tg, *shape) if tg is not None else None)

@@ -5,6 +5,7 @@ A stub call checks what a launch needs: the memory behind its workspace
 pointer still belongs to a live tensor when the call is made."""
 import collections
 import threading
+import time
 import weakref
 
 import pytest
@@ -134,3 +135,22 @@ def test_eviction_by_other_calls_keeps_the_workspace(layer):
     _run([lambda: call(64), others])
     assert seen == [True]
     assert len(mb._PREPARED) == mb._PREPARED_MAX
+
+
+def test_calls_on_one_workspace_do_not_interleave(layer):
+    """A call may launch several kernels that hand values on in its workspace:
+    another thread's call on that workspace waits until it has returned."""
+    install, call = layer
+    inside = [0]
+    most = [0]
+
+    def launch(T, pointer):
+        inside[0] += 1
+        most[0] = max(most[0], inside[0])
+        time.sleep(0.1)
+        inside[0] -= 1
+
+    install(launch=launch)
+    call(64)
+    _run([lambda: call(64)] * 3)
+    assert most[0] == 1
