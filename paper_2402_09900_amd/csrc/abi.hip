@@ -70,7 +70,7 @@ uint64_t layout_sig(std::initializer_list<int64_t> vals) {
 
 // entry points in a signature
 enum SigKind : int64_t { kSigDiag = 1, kSigDiagBwd, kSigFfm, kSigFfmBwd, kSigDiscount, kSigTbbBegins,
-                         kSigTbbSample };
+                         kSigLinattn, kSigLinattnBwd, kSigTbbSample };
 
 // Tiling and workspace layout of a diagonal scan.  `vec` selects the
 // vectorised lane width; `state_complex` picks the descriptor size.
@@ -716,10 +716,10 @@ bool plan_linattn(int64_t T, int64_t H, LinPlan* p) {
 // Extents the kernels address: 32-bit offsets inside a block's rows, the grid.
 bool lin_extents_ok(int64_t T, int64_t H) { return T <= (int64_t)INT32_MAX / 2 && H <= 65535; }
 
-// Forward states of every segment, scanned, with the workspace's header and
-// count words prepared.
+// Forward states of every segment, scanned, with the workspace's header (bound
+// to sig) and count words prepared.
 int lin_states(const float* k, const float* v, const uint8_t* start, int64_t T, int64_t H, const LinPlan& p, char* ws,
-               hipStream_t s) {
+               uint64_t sig, hipStream_t s) {
     LinSummaryArgs sa{};
     sa.k = k;
     sa.v = v;
@@ -731,6 +731,7 @@ int lin_states(const float* k, const float* v, const uint8_t* start, int64_t T, 
     sa.chunks = p.chunks;
     sa.fill = (u32x4*)ws;
     sa.fill16 = (int64_t)(p.off_states / 16);
+    sa.sig = sig;
     if (linattn_summary_launch(sa, p.nseg, s) != hipSuccess) return MEMOROID_EHIP;
     if (p.nseg <= kLinDirectSegs) return MEMOROID_OK;
     LinScanArgs ca{};
@@ -772,7 +773,7 @@ int memoroid_scan_linattn(const float* q, const float* k, const float* v, const 
     if (!aligned(workspace, 256)) return MEMOROID_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     char* ws = (char*)workspace;
-    const int st = lin_states(k, v, start, T, H, p, ws, s);
+    const int st = lin_states(k, v, start, T, H, p, ws, layout_sig({kSigLinattn, T, H}), s);
     if (st != MEMOROID_OK) return st;
     LinOutputArgs oa{};
     oa.q = q;
@@ -853,7 +854,7 @@ int memoroid_scan_linattn_bwd(const float* q, const float* k, const float* v, co
     const LinPlan& f = p.fwd;
 
     // forward segment states (as in the forward pass, without the readout)
-    const int st = lin_states(k, v, start, T, H, f, ws, s);
+    const int st = lin_states(k, v, start, T, H, f, ws, layout_sig({kSigLinattnBwd, T, H}), s);
     if (st != MEMOROID_OK) return st;
 
     LinBwdArgs ba{};

@@ -220,6 +220,7 @@ struct LinSummaryArgs {
     int32_t chunks;
     u32x4* fill;        // header and count words to prepare (all-ones bytes, 16-byte units)
     int64_t fill16;
+    uint64_t sig;       // the header's signature: a *_prepared call must not take the workspace for a fresh one
 };
 
 struct LinScanArgs {

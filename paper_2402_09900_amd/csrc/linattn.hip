@@ -41,13 +41,15 @@ __global__ __launch_bounds__(256, 4) void linattn_summary_kernel(LinSummaryArgs 
     __shared__ __attribute__((aligned(16))) float sV[2][kTileF];
     const int64_t seg = blockIdx.x, h = blockIdx.y;
     const LinLane L;
-    // header and episode-index count words, prepared (all-ones bytes) for the
-    // later kernels (stream order)
+    // header and episode-index count words, prepared (all-ones bytes, and the
+    // call's signature in the header) for the later kernels (stream order)
     {
         const int64_t nblk = (int64_t)gridDim.x * gridDim.y;
         const int64_t gid = (int64_t)(blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
         const u32x4 ones = {kEmpty32, kEmpty32, kEmpty32, kEmpty32};
-        for (int64_t i = gid; i < p.fill16; i += nblk * 256) p.fill[i] = ones;
+        static_assert(offsetof(WsHeader, sig) == 8, "the signature is the second half of the first unit");
+        const u32x4 head = {kEmpty32, kEmpty32, (uint32_t)p.sig, (uint32_t)(p.sig >> 32)};
+        for (int64_t i = gid; i < p.fill16; i += nblk * 256) p.fill[i] = i == 0 ? head : ones;
     }
     const int64_t seg0 = seg * p.chunks * kChunk;
     // V goes through LDS (every wavefront takes all of its columns), the

@@ -295,6 +295,31 @@ def test_binding_cache_reuses_prepared_workspaces():
         assert cond_err(h.cpu().numpy(), ref, m) <= TOL, call
 
 
+@pytest.mark.parametrize("grad", [False, True])
+def test_prepared_call_on_a_linear_attention_workspace_reports_mismatch(grad):
+    """Linear attention leaves its own signature in the header: a prepared call
+    that follows without a preparation stands down, instead of taking the
+    states for descriptors."""
+    T, H, d = 1500, 4, 64
+    op = mb.OP_LINATTN_BWD if grad else mb.OP_LINATTN
+    n = max(mb.memoroid_workspace_bytes(op, 1, T, H, 64, 64, 64), mb.memoroid_workspace_bytes(mb.OP_DIAG, 1, T, d, 0, 0, 0))
+    ws = garbage(n, 13)
+    la = tapes.make_linattn(3, seed=1401, T=T, H=H)
+    q, k, v, s = dev(la.q), dev(la.k), dev(la.v), dev(la.start)
+    announce("workspace linattn grad=%s then a prepared diag call" % grad)
+    out = mb.scan_linattn(q, k, v, s, workspace=ws)
+    if grad:
+        mb.scan_linattn_bwd(q, k, v, s, out, torch.ones_like(out), workspace=ws)
+    assert status(ws) == mb.OK
+    w = tapes.make_custom_diag("f32", 1, T, d, False, seed=1402, with_grad=False)
+    a, x, st = dev(w.a), dev(w.x), dev(w.start)
+    h = torch.full((1, T, d), 7.0, dtype=torch.float32, device=DEV)
+    assert mb.memoroid_scan_diag_prepared(a.data_ptr(), d, x.data_ptr(), st.data_ptr(), h.data_ptr(), None, 1, T, d,
+                                          mb.F32, mb.F32, ws.data_ptr(), ws.numel(), stream()) == mb.OK
+    assert status(ws) == mb.EMISMATCH
+    assert bool((h == 7.0).all())
+
+
 # ------------------------------------------------- self-initialising calls
 
 
