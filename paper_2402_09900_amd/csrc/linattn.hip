@@ -53,21 +53,25 @@ __global__ __launch_bounds__(256, 4) void linattn_summary_kernel(LinSummaryArgs 
     }
     const int64_t seg0 = seg * p.chunks * kChunk;
     // V goes through LDS (every wavefront takes all of its columns), the
-    // wavefront's 16 columns of K straight to registers
+    // wavefront's 16 columns of K straight to registers; a chunk ahead, K block
+    // by block as the registers become free
     Frag vreg, kreg;
     uint32_t flag;
-    auto fetch = [&](int ch) {
+    auto fetch_v = [&](int ch) {
         const int64_t t0 = seg0 + (int64_t)ch * kChunk;
         const bool have = ch < p.chunks;
         flag = fetch_flag(p.start, have ? t0 : 0, have ? p.T : 0);
         fetch_chunk(vreg, chunk_rows(p.v, t0, p.T, p.H, h, have), L);
-        const ChunkRows ck = chunk_rows(p.k, t0, p.T, p.H, h, have);
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) kreg[b][q] = ck.load1(16 * b + 4 * L.g + q, 16 * L.w + L.c);
     };
-    fetch(0);
+    auto fetch_k = [&](int ch, int b) {
+        const int64_t t0 = seg0 + (int64_t)ch * kChunk + 16 * b;
+        const ChunkRows ck = chunk_rows(p.k, t0, p.T, p.H, h, ch < p.chunks);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) kreg[b][q] = ck.load1(4 * L.g + q, 16 * L.w + L.c);
+    };
+    fetch_v(0);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) fetch_k(0, b);
     Frag st;                                   // st[s][r] = dS[16 w + c][16 r + 4 g + s]
 #pragma unroll
     for (int s = 0; s < 4; ++s) st[s] = zero4();
@@ -77,28 +81,27 @@ __global__ __launch_bounds__(256, 4) void linattn_summary_kernel(LinSummaryArgs 
     for (int ch = 0; ch < p.chunks; ++ch) {
         float* const sv = sV[ch & 1];
         stage_chunk<false>(sv, vreg, L);
-        Frag kc;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) kc[b] = phi4(kreg[b]);
         const uint64_t m = begin_bits(flag, seg0 + (int64_t)ch * kChunk, p.T);
         any = any || m != 0;
         barrier_lds();
-        fetch(ch + 1);
+        fetch_v(ch + 1);
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const uint32_t mb = block_bits(m, b);
             Frag vc;
             lds_cf(vc, sv, 16 * b, L);
+            f32x4 kc = phi4(kreg[b]);
+            fetch_k(ch + 1, b);
             if (mb) {
                 const uint32_t keep = bit_range(31 - __builtin_clz(mb), kBlk);
                 select_rows(vc, keep, L);
-                select_rows(kc[b], keep, L);
+                select_rows(kc, keep, L);
 #pragma unroll
                 for (int s = 0; s < 4; ++s) st[s] = zero4();
                 z = 0.0f;
             }
-            z += (kc[b].x + kc[b].y) + (kc[b].z + kc[b].w);
-            state_add(st, vc, kc[b]);
+            z += (kc.x + kc.y) + (kc.z + kc.w);
+            state_add_once(st, vc, kc);
         }
     }
     float* const out = p.states + (seg * p.H + h) * kStateWords;

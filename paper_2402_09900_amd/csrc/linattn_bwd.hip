@@ -188,9 +188,11 @@ __global__ __launch_bounds__(256, 2) void linattn_dq_kernel(LinBwdArgs p) {
                     select_rows(ds, keep, L);
                     head = false;
                 }
-                state_add(us, x, qs);
+                state_add_once(us, x, qs);
+                float wb = 0.0f;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) ws = __builtin_fmaf(ds[q], qs[q], ws);
+                for (int q = 0; q < 4; ++q) wb = __builtin_fmaf(ds[q], qs[q], wb);
+                ws += wb;
             }
             lds_cf(x, sV, 16 * b, L);
             if (mb) {
@@ -200,7 +202,7 @@ __global__ __launch_bounds__(256, 2) void linattn_dq_kernel(LinBwdArgs p) {
 #pragma unroll
                 for (int s = 0; s < 4; ++s) st[s] = zero4();
             }
-            state_add(st, x, ks);
+            state_add_once(st, x, ks);
         }
         // every wavefront has read all of z before the chunk (it is past the
         // barrier above) but its own quarter, which it rewrites here
@@ -358,7 +360,7 @@ __global__ __launch_bounds__(256, 2) void linattn_dkv_kernel(LinBwdArgs p) {
                     uv[s] = zero4();
                 }
             }
-            state_add(uk, x, qs);
+            state_add_once(uk, x, qs);
             state_add(uv, y, ds);
         }
         barrier_lds();
