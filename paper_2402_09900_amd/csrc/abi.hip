@@ -209,12 +209,12 @@ void set_scan_ws(Args& a, const DiagPlan& p, char* base, WsHeader* hdr, uint64_t
     a.ctr = (uint32_t*)(base + p.off_ctr);
 }
 
-// Cache policy of a diagonal scan from its row of d features and the tensors it
-// reads (infinite: kStreamOut is no choice); kernels.hpp says why the lines lie
+// Cache policy of a diagonal scan from its row of d features and a tensor of
+// them (infinite: kStreamOut is no choice); kernels.hpp says why the lines lie
 // there.
-int cache_policy(int64_t row_bytes, double input_bytes) {
+int cache_policy(int64_t row_bytes, double tensor_bytes) {
     if (row_bytes % kChainRowBytes != 0) return kCached;
-    return input_bytes <= (double)kCachedInputBytes ? kStreamOut : kStreamAll;
+    return tensor_bytes <= (double)kCachedTensorBytes ? kStreamOut : kStreamAll;
 }
 
 bool diag_dtypes_ok(int in_dt, int out_dt) {
@@ -330,7 +330,7 @@ static int scan_diag_run(const void* a, int64_t a_stride_t, const void* x, const
     args.Qp = p.Qp;
     args.nfb = p.nfb;
     args.nchains = (int32_t)p.nchains;
-    args.policy = cache_policy(d * ib, (double)BTd * ib * (ainv ? 1 : 2));
+    args.policy = cache_policy(d * ib, (double)BTd * ib);
     set_scan_ws(args, p, ws, (WsHeader*)ws, layout_sig({kSigDiag, B, T, d, sd, vec, ainv}));
     args.idx = episode_idx;
     args.cnt = (uint64_t*)(ws + p.off_cnt);
@@ -635,7 +635,7 @@ static int scan_diag_bwd_run(const void* a, int64_t a_stride_t, const uint8_t* s
     args.Qp = p.Qp;
     args.nfb = p.nfb;
     args.nchains = (int32_t)p.nchains;
-    args.policy = cache_policy(d * eb, ainv ? INFINITY : (double)BTd * eb * (grad_a ? 3 : 2));
+    args.policy = cache_policy(d * eb, ainv ? INFINITY : (double)BTd * eb);
     set_scan_ws(args, p, ws, (WsHeader*)ws,
                 layout_sig({kSigDiagBwd, B, T, d, dtype, vec, ainv, grad_a != nullptr}));
     const int k = dtype == MEMOROID_F32 ? K_F32 : K_C64;

@@ -83,19 +83,26 @@ constexpr int kFfmFwdRows = MEMOROID_FFM_FWD_ROWS;
 //     features of two chains (or two rows), and a non-temporal access drops or
 //     writes it once for each: f32 8 x 30000 x 51 67 / 129 -> 43 / 70, complex
 //     105 / 143 -> 55 / 97 with an invariant a, f32 65536 x 100 34 / 68 -> 26 / 43.
-//   kStreamOut: whole lines, inputs up to kCachedInputBytes.  Outputs go past
-//     the caches and inputs through them, so that what the 256 MB Infinity
-//     Cache holds of an input is found there: forward and reverse with a per
-//     step, T = 16384, 32768, 65536 x 256, f32 39 / 67 / 115 -> 36 / 58 / 101
-//     with the same buffers each time; with buffers that no cache holds 39.4 /
-//     67.7 / 115.5 -> 38.9 / 67.6 / 113.6.
-//   kStreamAll: larger inputs (f32 2^18 x 256 387 against 389 with cached
-//     loads, complex 720 against 734), and the reverse scan with an invariant
-//     a, which cached loads slow by 3 % at every size when no cache holds its
-//     inputs (forward and reverse, f32 16384 x 256 27.2 -> 28.8, complex 65536
-//     x 256 132 -> 135).
+//   kStreamOut: whole lines, tensors of up to kCachedTensorBytes.  Outputs go
+//     past the caches and inputs through them, so that what the 256 MB Infinity
+//     Cache holds of an input is found there: a layer's inputs that the kernels
+//     before it wrote, a and h in the reverse scan after the forward one.  A
+//     chain of kernels that write a and x, the forward scan, a kernel that
+//     writes g and the reverse scan, all with a per step, against kStreamAll:
+//     tensors of 16 / 32 / 64 MiB f32 83 / 112 / 190 -> 79 / 105 / 182, complex
+//     81 / 114 / 193 -> 78 / 108 / 190; the reverse scan alone 28 / 42 / 69 ->
+//     23 / 34 / 61 in it.  Called again on the same buffers, forward / reverse
+//     10 to 30 % faster.  On inputs that no cache holds 2 to 5 % slower each,
+//     but the two after one another 1 to 3 % faster.
+//   kStreamAll: larger tensors.  Cached loads then push out what the next kernel
+//     would have found: in that chain 80 MiB 222 -> 224 (complex 225 -> 230),
+//     160 MiB 416 -> 435, the forward scan alone 102 -> 122; with an invariant a
+//     equal up to 64 MiB, 128 MiB complex 225 -> 230, 256 MiB 417 -> 439.  And
+//     the reverse scan with an invariant a, which cached loads slow by 3 % at
+//     every size when no cache holds its inputs (forward and reverse, f32
+//     16384 x 256 27.2 -> 28.8, complex 65536 x 256 132 -> 135).
 enum CachePolicy { kCached = 0, kStreamOut = 1, kStreamAll = 2 };
-constexpr int64_t kCachedInputBytes = (int64_t)320 << 20;
+constexpr int64_t kCachedTensorBytes = (int64_t)64 << 20;
 
 struct DiagFwdArgs {
     const void* a;
