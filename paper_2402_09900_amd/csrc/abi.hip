@@ -414,7 +414,7 @@ static int scan_ffm_run(const float* alpha, const float* omega, const float* x, 
     args.Qp = p.Qp;
     args.nfb = p.nfb;
     args.nchains = (int32_t)p.nchains;
-    args.policy = cache_policy(d * 8, (double)BTd / (double)c * 4);
+    args.policy = cache_policy(d * 8, INFINITY);
     set_scan_ws(args, p, ws, (WsHeader*)ws, layout_sig({kSigFfm, B, T, m, c, vec}));
     args.idx = episode_idx;
     args.cnt = (uint64_t*)(ws + p.off_cnt);

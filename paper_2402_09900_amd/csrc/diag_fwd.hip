@@ -465,11 +465,11 @@ static void launch_fwd_pol(const DiagFwdArgs& args, unsigned grid, hipStream_t s
     const dim3 g(grid), block(256);
     if (args.policy == kCached)
         hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, AINV, QP, kCached, FFM>), g, block, 0, s, args);
-    else if (QP == 0 || args.policy == kStreamAll)     // no kStreamOut for the rarer plans
+    else if (QP == 0 || FFM || args.policy == kStreamAll)     // no kStreamOut for the rarer plans and FFM's own loads
         hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, AINV, QP, kStreamAll, FFM>), g, block, 0, s, args);
     else
-        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, AINV, QP, QP ? kStreamOut : kStreamAll, FFM>), g, block, 0,
-                           s, args);
+        hipLaunchKernelGGL((diag_fwd_kernel<IN, OUT, VEC, R, AINV, QP, QP && !FFM ? kStreamOut : kStreamAll, FFM>), g,
+                           block, 0, s, args);
 }
 template <Kind IN, Kind OUT, int VEC, int R, bool AINV, bool FFM = false>
 static void launch_fwd_qp(const DiagFwdArgs& args, unsigned grid, hipStream_t s) {
