@@ -693,9 +693,6 @@ struct LinPlan {
     size_t off_cnt = 0, off_states = 0, off_R = 0, total = 0;
 };
 
-// heads of one call: a bound on the state row (kLinStateWords floats a head)
-constexpr int64_t kLinMaxHeads = 251;
-
 bool plan_linattn(int64_t T, int64_t H, LinPlan* p) {
     if (H > kLinMaxHeads) return false;
     p->chunks = lin_chunks(T, H);

@@ -216,6 +216,15 @@ constexpr int kLinStateWords = 64 * 64 + 64;
 constexpr int kLinDirectSegs = 8;
 static_assert(kLinDirectSegs <= 64, "a segment's flag is a bit of a 64-bit word");
 
+// The state scan takes kLinScanGroups * rows segments at a time, rows at most
+// kLinScanMaxRows, and addresses them with 32-bit offsets below 2^31 (a buffer
+// resource's largest range): 512 segments of 251 heads are 2138439680 bytes.
+// (252 would still fit; callers have always been refused there.)
+constexpr int kLinScanGroups = 32, kLinScanMaxRows = 16;
+constexpr int64_t kLinMaxHeads = 251;
+static_assert(kLinScanGroups * kLinScanMaxRows * kLinMaxHeads * kLinStateWords * 4 < INT32_MAX,
+              "a tile of the state scan is addressed with 32-bit offsets");
+
 struct LinSummaryArgs {
     const float* k;
     const float* v;

@@ -122,11 +122,12 @@ __global__ __launch_bounds__(256, 4) void linattn_summary_kernel(LinSummaryArgs 
 // once: the scan is one read and one write of the states (128 segments of 4
 // heads 6.3 us, 512 segments 12.8 us = 5.3 TB/s; predicated pointer loads took
 // 12 us on 256 segments against 8.6).
-constexpr int kScanCols = 8, kScanGroups = 32;
+constexpr int kScanCols = 8, kScanGroups = kLinScanGroups;
 template <int RPT, bool REV>
 __global__ __launch_bounds__(256) void state_scan_kernel(LinScanArgs p) {
     __shared__ f32x4 s_tot[kScanGroups][kScanCols];
     __shared__ uint32_t s_flag[kScanGroups];
+    static_assert(RPT <= kLinScanMaxRows, "kLinMaxHeads follows from the largest tile");
     constexpr int kTile = kScanGroups * RPT;
     const int col = threadIdx.x % kScanCols, grp = threadIdx.x / kScanCols;
     const uint32_t row_bytes = (uint32_t)(p.width * 4);
@@ -365,7 +366,7 @@ static void scan_launch(const LinScanArgs& a, hipStream_t s) {
     if (a.n <= 2 * kScanGroups) hipLaunchKernelGGL((state_scan_kernel<2, REV>), grid, block, 0, s, a);
     else if (a.n <= 4 * kScanGroups) hipLaunchKernelGGL((state_scan_kernel<4, REV>), grid, block, 0, s, a);
     else if (a.n <= 8 * kScanGroups) hipLaunchKernelGGL((state_scan_kernel<8, REV>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((state_scan_kernel<16, REV>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((state_scan_kernel<kLinScanMaxRows, REV>), grid, block, 0, s, a);
 }
 
 hipError_t linattn_scan_launch(bool rev, const LinScanArgs& a, hipStream_t s) {

@@ -143,6 +143,10 @@ def test_workspace_queries():
     h = mb.memoroid_scan_linattn_workspace_bytes
     assert h(32768, 4, 64, 64, 64) > 0
     assert h(32768, 4, 32, 64, 64) == 0
+    # heads up to what a tile of the state scan addresses with 32-bit offsets
+    hb = mb.memoroid_scan_linattn_bwd_workspace_bytes
+    assert h(1 << 20, 251, 64, 64, 64) > 0 and hb(1 << 20, 251, 64, 64, 64) > 0
+    assert h(64, 252, 64, 64, 64) == 0 and hb(64, 252, 64, 64, 64) == 0
     # descriptor storage grows linearly in T
     assert f(1, 1 << 21, 256, mb.F32, mb.F32) < 2.2 * f(1, 1 << 20, 256, mb.F32, mb.F32)
 
