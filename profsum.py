@@ -14,6 +14,7 @@ same figures scaled by what the counters read for the run's plain device copy
 library call bench.py times (the sum over the kernels the call launches,
 CALLS below), with the hash of the HIP sources they were measured on.
 """
+import re
 import sqlite3
 import statistics
 import sys
@@ -102,10 +103,10 @@ def source_hash(root):
 
 
 
-# kernels each timed library call launches (name after "memoroid::"), per
-# workload, once per call
+# kernels each timed library call launches (a regular expression for what
+# follows "memoroid::" in its name), per workload, once per call
 _DIAG = {"fwd": ["diag_fwd_kernel"], "bwd": ["diag_bwd_kernel"]}
-_LIN_FWD = ["linattn_summary_kernel", "state_scan_kernel", "linattn_output_kernel"]
+_LIN_FWD = ["linattn_summary_kernel", r"state_scan_kernel<\d+, false>", "linattn_output_kernel"]
 CALLS = {
     2: _DIAG,
     4: {"fwd": ["diag_fwd_kernel"]},
@@ -116,8 +117,8 @@ CALLS = {
         "sample": ["tbb_rows_kernel", "tbb_gather_kernel"]},
     3: {"linattn_fwd": _LIN_FWD},
     9: {"linattn_fwd": _LIN_FWD,
-        "linattn_bwd": ["linattn_summary_kernel", "state_scan_kernel", "linattn_dq_kernel", "state_scan_kernel",
-                        "linattn_dkv_kernel"]},
+        "linattn_bwd": ["linattn_summary_kernel", r"state_scan_kernel<\d+, false>", "linattn_dq_kernel",
+                        r"state_scan_kernel<\d+, true>", "linattn_dkv_kernel"]},
 }
 
 
@@ -174,7 +175,7 @@ def call_bytes(key, fdb, wdb):
     for call, kernels in CALLS[key].items():
         total = 0.0
         for kname in kernels:
-            hits = [v for k, v in per.items() if ("memoroid::" + kname) in k]
+            hits = [v for k, v in per.items() if re.search("memoroid::" + kname, k)]
             if len(hits) != 1:
                 raise SystemExit("workload %d call %s: kernel %s matched %d entries" % (key, call, kname, len(hits)))
             total += hits[0]
