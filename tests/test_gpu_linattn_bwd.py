@@ -158,6 +158,75 @@ def test_nonfinite_values_stay_in_their_episode():
         assert e <= TOL, (name, e)
 
 
+# (T, H, rows of a segment): 13 segments of one chunk and 16 of two, scanned,
+# nine of four, scanned, and eight of two, added up by their readers
+SEGMENTED = [(64 * 12 + 9, 2, 64), (2048 - 13, 32, 128), (2048 + 17, 64, 256), (1024 - 5, 64, 128)]
+
+
+@pytest.mark.parametrize("T,H,rows", SEGMENTED)
+def test_nonfinite_values_beside_segment_edges(T, H, rows):
+    """Values that are not finite in the last and the first row of segments and
+    of chunks inside them, in episodes that cross the edges: they reach the
+    rest of their episode, over the states of the scan and of the walk, and
+    nothing else (as the test above)."""
+    la = tapes.make_linattn(3, seed=92 + H, T=T, H=H)
+    f = np.zeros(T, np.uint8)
+    f[[0, rows - 10, rows + 7, 2 * rows, 3 * rows - 1, 3 * rows + 33, 5 * rows + 3, T - 12]] = 1
+    la.start = f
+    g = grad_input(la, 10)
+    la.k[rows - 1, 0, 3] = np.nan          # last row of a segment, episode over its edge
+    la.v[2 * rows, H - 1, 7] = np.inf      # begin step on an edge
+    la.q[3 * rows, 0, 5] = np.nan          # first row of a segment, episode from the row before
+    la.k[4 * rows - 1, 0, 9] = np.nan      # an episode over two edges, from the first on
+    g[4 * rows + 1, H - 1, 11] = np.nan    # the same episode in another head, and back over its first edge
+    la.v[T - 1, 0, 2] = np.nan             # last step of the tape
+    announce("linattn bwd non-finite beside segment edges T=%d H=%d" % (T, H))
+    q, k, v, s = dev(la.q), dev(la.k), dev(la.v), dev(la.start)
+    out = mb.scan_linattn(q, k, v, s)
+    gq, gk, gv = mb.scan_linattn_bwd(q, k, v, s, out, dev(g))
+    torch.cuda.synchronize()
+    wide = [a.astype(np.float64) for a in (la.q, la.k, la.v)]
+    ro, mo = oracle.linattn(*wide, la.start)
+    rq, rk, rv, mq, mk, mv = oracle.linattn_bwd(*wide, la.start, g.astype(np.float64))
+    for name, got, ref, m in (("out", out, ro, mo), ("dq", gq, rq, mq), ("dk", gk, rk, mk), ("dv", gv, rv, mv)):
+        got = got.cpu().numpy()
+        fin = np.isfinite(ref)
+        assert (~fin).any(), name
+        assert np.isfinite(got[fin]).all(), (name, np.argwhere(fin & ~np.isfinite(got))[:5])
+        assert not np.isfinite(got[~fin]).any(), (name, np.argwhere(~fin & np.isfinite(got))[:5])
+        e = cond_err(got[fin], ref[fin], m[fin])
+        assert e <= TOL, (name, e)
+
+
+@pytest.mark.parametrize("kind", ["short", "all_begins", "single_episode", "chunk_starts", "chunk_second_rows",
+                                  "segment_starts", "flag_bytes"])
+def test_flag_patterns_in_segments_of_two_chunks(kind):
+    T, H, rows = SEGMENTED[1]
+    rng = np.random.default_rng(18)
+    la = tapes.make_linattn(3, seed=78, T=T, H=H)
+    f = np.zeros(T, np.uint8)
+    if kind == "short":
+        f = tapes.flags_from_lengths(rng.integers(1, 40, size=T), T)
+    elif kind == "all_begins":
+        f[:] = 1
+    elif kind == "chunk_starts":
+        f[::64] = 1
+    elif kind == "chunk_second_rows":
+        f[1::64] = 1
+    elif kind == "segment_starts":
+        f[::rows] = 1
+    elif kind == "flag_bytes":
+        f = (rng.random(T) < 0.01).astype(np.uint8) * rng.integers(1, 256, size=T).astype(np.uint8)
+    check(_with_flags(la, f), kind + ", two chunks a segment")
+
+
+@pytest.mark.parametrize("T,H", [(2048 + 17, 64), (1024, 64), (1024 - 5, 64)])
+def test_segments_of_several_chunks(T, H):
+    """Nine segments of four chunks, scanned, the last one short; eight of two,
+    added up by their readers, whole and with a partial last chunk."""
+    check(tapes.make_linattn(3, seed=600 + T, T=T, H=H), "several chunks a segment")
+
+
 def test_errors_do_not_grow_with_the_episode():
     """One episode over the whole tape, in segments of eight chunks: the
     2-norm errors of 262144 steps stay within 1.5 times those of 1024.  What
