@@ -671,20 +671,30 @@ int memoroid_scan_diag_bwd_prepared(const void* a, int64_t a_stride_t, const uin
 
 namespace {
 
-// 64-row chunks per segment (1, 2, 4 or 8).  A workgroup walks a segment, so
-// longer segments write and read fewer states (16.6 KB each) but leave fewer
-// workgroups: a segment doubles as long as MEMOROID_LIN_MIN_GROUPS remain, two
-// per CU (forward / gradient in us with at least 256, 512 and 1024 workgroups:
-// T = 32768, 4 heads 71 / 166, 64 / 152, 67 / 164; T = 16384 42 / 94, 42 / 92,
-// 44 / 104; T = 49152, 8 heads 157 / 414, 157 / 413, 167 / 420).
-#ifndef MEMOROID_LIN_MIN_GROUPS
-#define MEMOROID_LIN_MIN_GROUPS 512
-#endif
+// 64-row chunks per segment (1 to 8).  A workgroup walks a segment, so a pass
+// takes as long as the most loaded of the 256 CUs: ceil(workgroups / 256)
+// segments of c chunks, each with a start and an end (states, first loads) worth
+// 0.4 of a chunk.  A CU with a single workgroup needs a quarter more per chunk,
+// since nothing runs beside it.  The c with the shortest such time is taken: a
+// rule that only asked for at least 512 workgroups, two per CU, left a last
+// round nearly empty (forward / gradient in us, that rule -> this one; with one
+// workgroup per chunk and the states through a look-back scan in brackets):
+// T = 18000, 8 heads (568 -> 752 workgroups) 84 / 218 -> 75 / 179 (82 / 221);
+// T = 25000, 8 heads (784 -> 448) 114 / 260 -> 101 / 235 (108 / 294);
+// T = 20000, 4 heads (628 -> 420) 52 / 127 -> 52 / 114 (50 / 136).
 int lin_chunks(int64_t T, int64_t H) {
     const int64_t n = (T + kLinChunkRows - 1) / kLinChunkRows;
-    int c = 1;
-    while (c < 8 && (n + 2 * c - 1) / (2 * c) * H >= MEMOROID_LIN_MIN_GROUPS) c *= 2;
-    return c;
+    int best = 1;
+    int64_t best_cost = INT64_MAX;
+    for (int c = 1; c <= 8; ++c) {
+        const int64_t per_cu = ((n + c - 1) / c * H + 255) / 256;
+        const int64_t cost = per_cu * (10 * c + 4) * (per_cu == 1 ? 5 : 4);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = c;
+        }
+    }
+    return best;
 }
 
 struct LinPlan {

@@ -159,8 +159,8 @@ def test_nonfinite_values_stay_in_their_episode():
 
 
 # (T, H, rows of a segment): 13 segments of one chunk and 16 of two, scanned,
-# nine of four, scanned, and eight of two, added up by their readers
-SEGMENTED = [(64 * 12 + 9, 2, 64), (2048 - 13, 32, 128), (2048 + 17, 64, 256), (1024 - 5, 64, 128)]
+# eleven of three, scanned, and eight of two, added up by their readers
+SEGMENTED = [(64 * 12 + 9, 2, 64), (2048 - 13, 32, 128), (2048 + 17, 64, 192), (1024 - 5, 64, 128)]
 
 
 @pytest.mark.parametrize("T,H,rows", SEGMENTED)
@@ -222,7 +222,7 @@ def test_flag_patterns_in_segments_of_two_chunks(kind):
 
 @pytest.mark.parametrize("T,H", [(2048 + 17, 64), (1024, 64), (1024 - 5, 64)])
 def test_segments_of_several_chunks(T, H):
-    """Nine segments of four chunks, scanned, the last one short; eight of two,
+    """Eleven segments of three chunks, scanned, the last partial; eight of two,
     added up by their readers, whole and with a partial last chunk."""
     check(tapes.make_linattn(3, seed=600 + T, T=T, H=H), "several chunks a segment")
 

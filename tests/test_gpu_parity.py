@@ -187,7 +187,7 @@ def test_workload3_short_episodes():
 
 @pytest.mark.parametrize("T,H", [(2048 - 13, 32), (2048 + 17, 64), (1024 - 5, 64)])
 def test_linattn_segments_of_several_chunks(T, H):
-    """16 segments of two chunks and nine of four, scanned, and eight of two,
+    """16 segments of two chunks and eleven of three, scanned, and eight of two,
     added up by their readers; the last segment short, its last chunk partial."""
     check_linattn(tapes.make_linattn(T=T, H=H, seed=105 + H), "several chunks a segment")
 
