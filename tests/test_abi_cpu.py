@@ -152,15 +152,15 @@ def test_workspace_queries():
     assert h(1 << 20, 251, 64, 64, 64) > 0 and hb(1 << 20, 251, 64, 64, 64) > 0
     assert h(64, 252, 64, 64, 64) == 0 and hb(64, 252, 64, 64, 64) == 0
     # the workgroups of a call (segments of c chunks and heads) fill the rounds
-    # that 256 CUs take them in: no CU has more than 1.34 times its share (the
-    # lowest bound: 769 chunks are 1.33 at best)
-    for T, H in ((18000, 8), (20000, 4), (25000, 8), (30000, 8), (36000, 4), (49152, 3), (100000, 1), (100000, 2)):
+    # that 256 CUs take them in: no CU has more than 1.15 times its share (with
+    # the longest segments that leave 512 workgroups these have 1.31 to 1.36)
+    for T, H in ((18000, 8), (25000, 8), (36000, 4), (49152, 3), (100000, 2)):
         seg = [s for s in range(1, T // 64 + 2)
                if h(T, H, 64, 64, 64) == 256 + _up(8 * s) + _up(s * H * 4160 * 4) + _up(s)]
         n = -(-T // 64)
         assert len(seg) == 1, (T, H, seg)
         c = min(c for c in range(1, 9) if -(-n // c) == seg[0])
-        assert -(-seg[0] * H // 256) * c <= 1.34 * n * H / 256, (T, H, c)
+        assert -(-seg[0] * H // 256) * c <= 1.15 * n * H / 256, (T, H, c)
     # descriptor storage grows linearly in T
     assert f(1, 1 << 21, 256, mb.F32, mb.F32) < 2.2 * f(1, 1 << 20, 256, mb.F32, mb.F32)
 
