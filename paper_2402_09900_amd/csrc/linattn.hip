@@ -26,17 +26,18 @@
 // for the layouts that let a block's products and the state meet in registers.
 //
 // Measured against one workgroup per 64-row chunk with every chunk's state
-// through memory and a look-back scan over them (T = 32768, 4 heads): forward
-// 74 -> 64 us (summary 23 -> 19, scan 15 -> 6.3, output 41 -> 41), gradient
-// 198 -> 152 us; T = 1000: 22 -> 19 and 45 -> 37 us.
+// through memory and a look-back scan over them (T = 32768, 4 heads, calls one
+// after another): forward 72 -> 66 us, gradient 196 -> 154 us; T = 1000: 21 -> 18
+// and 45 -> 37 us.  Kernels in a trace over several sets of buffers (T = 32768):
+// summary 23 -> 21, scan 15 -> 6.6, output 49 -> 46 us.
 #include "linattn_common.hpp"
 
 namespace memoroid {
 
 // ---------------------------------------------------------------- summaries
-// Bound by instruction issue and its fixed start and end (18 us at T = 32768,
-// 4 heads, also with every load served by the L2; its reads take 11 us at copy
-// speed and its MFMAs 7).
+// Bound by instruction issue and its fixed start and end (19 us at T = 32768,
+// 4 heads, no fewer with every load served by the L2; its reads take 11 us at
+// copy speed and its MFMAs 7).
 __global__ __launch_bounds__(256, 4) void linattn_summary_kernel(LinSummaryArgs p) {
     __shared__ __attribute__((aligned(16))) float sV[2][kTileF];
     const int64_t seg = blockIdx.x, h = blockIdx.y;
@@ -186,11 +187,11 @@ __global__ __launch_bounds__(256) void state_scan_kernel(LinScanArgs p) {
 // ------------------------------------------------------------------- output
 
 // Three workgroups' registers per CU; at T = 32768 and 4 heads the grid has two
-// per CU, MFMAs keep the matrix cores 47 % busy (41 us against 17 us of MFMA
-// and 25 us of traffic), the rest being the phases of a chunk (staging, A of
-// the own block, z and den) that two wavefronts per SIMD only partly overlap.
-// Loading V a phase earlier (43 us) or a branch-free path for chunks without
-// begin steps (41 us) gained nothing.
+// per CU, MFMAs keep the matrix cores 43 % busy, counted (43 us in a trace, 17 us
+// of MFMA and 25 us of traffic), the rest being the phases of a chunk (staging,
+// A of the own block, z and den) that two wavefronts per SIMD only partly
+// overlap.  Loading V a phase earlier (2 us slower) or a branch-free path for
+// chunks without begin steps (the same time) gained nothing.
 template <bool DIRECT>
 __global__ __launch_bounds__(256, 3) void linattn_output_kernel(LinOutputArgs p) {
     __shared__ __attribute__((aligned(16))) float sQ[kTileF];     // phi(Q)

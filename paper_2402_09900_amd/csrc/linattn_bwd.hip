@@ -25,9 +25,10 @@ namespace memoroid {
 
 // ------------------------------------------------------------------- dq
 // LDS: phi(Q), phi(K), V and dnum of the chunk (70 KB, two workgroups per CU).
-// T = 32768, 4 heads: 58 us, 240 MFMAs a chunk and wavefront (26 us of the
-// matrix cores); a separate backward-summary kernel and a dq product beside dk
-// and dv took 43 us and a good third of 108.
+// T = 32768, 4 heads: 62 us in a trace (64 over several sets of buffers), 227
+// MFMAs a chunk and wavefront (24 us, matrix cores 45 % busy, counted); a
+// separate backward-summary kernel and a dq product beside dk and dv took 44 us
+// and a good third of 110, over several sets of buffers too.
 template <bool DIRECT>
 __global__ __launch_bounds__(256, 2) void linattn_dq_kernel(LinBwdArgs p) {
     __shared__ __attribute__((aligned(16))) float sQ[kTileF], sK[kTileF], sV[kTileF], sD[kTileF];
@@ -219,9 +220,10 @@ __global__ __launch_bounds__(256, 2) void linattn_dq_kernel(LinBwdArgs p) {
 // LDS: phi(Q), phi(K), V and dnum of the chunk (70 KB, two workgroups per CU).
 // dk contracts U over its columns and dv over its rows, so U is kept in both
 // register layouts (64 MFMAs a chunk and wavefront more than one copy would
-// take).  T = 32768, 4 heads: 61 us, 320 MFMAs a chunk and wavefront, matrix
-// cores 62 % busy (54 us with every load served by the L2, 46 us with the
-// MFMAs replaced by single FMAs).
+// take).  T = 32768, 4 heads: 66 us in a trace (68 over several sets of
+// buffers), 320 MFMAs a chunk and wavefront (34 us, matrix cores 59 % busy,
+// counted).  Before block sums were formed apart, at 61 us a call: 54 us with
+// every load served by the L2, 46 us with the MFMAs replaced by single FMAs.
 template <bool DIRECT>
 __global__ __launch_bounds__(256, 2) void linattn_dkv_kernel(LinBwdArgs p) {
     __shared__ __attribute__((aligned(16))) float sQ[kTileF], sK[kTileF], sV[kTileF], sD[kTileF];
