@@ -124,6 +124,7 @@ CALLS = {
 
 MFMA_FLOPS = 2 * 16 * 16 * 4      # one v_mfma_f32_16x16x4_f32
 FP32_MFMA_PEAK = 157.3e12
+SIMDS_PER_ENGINE = 32             # 256 CUs of four, 32 shader engines
 
 
 def mfma(pmc_db, trace_db, waves_per_kernel, title, cmd):
@@ -131,7 +132,9 @@ def mfma(pmc_db, trace_db, waves_per_kernel, title, cmd):
     block samples one shader engine, so the counters give MFMA instructions
     per wavefront (SQ_INSTS_VALU_MFMA_F32 / SQ_WAVES); flops issued = that x
     the launch's wavefronts x 2048, over the kernel's mean traced duration
-    and the fp32 MFMA peak."""
+    and the fp32 MFMA peak.  Beside it the share of the kernel's own cycles in
+    which the matrix cores are busy, over a shader engine's SIMDs
+    (SQ_VALU_MFMA_BUSY_CYCLES / SQ_BUSY_CYCLES)."""
     c = {}
     con = sqlite3.connect(pmc_db)
     for k, name, v in con.execute("select name, counter_name, counter_value from pmc_events"):
@@ -142,8 +145,8 @@ def mfma(pmc_db, trace_db, waves_per_kernel, title, cmd):
         dur.setdefault(k, []).append((e0 - s0) * 1e-9)
     print("# %s\n\ncommand: `%s`\n" % (title, cmd))
     print("| kernel | wavefronts / launch | MFMA instr / wavefront | flops issued / launch | mean duration us "
-          "| issued TFLOP/s | % of fp32 MFMA peak |")
-    print("|---|---:|---:|---:|---:|---:|---:|")
+          "| issued TFLOP/s | % of fp32 MFMA peak | matrix cores busy % |")
+    print("|---|---:|---:|---:|---:|---:|---:|---:|")
     for k, nw in waves_per_kernel:
         full = [kk for kk in c if kk.startswith(k) or kk.startswith("void " + k)]
         if not full:
@@ -152,8 +155,10 @@ def mfma(pmc_db, trace_db, waves_per_kernel, title, cmd):
         per_wave = sum(d["SQ_INSTS_VALU_MFMA_F32"]) / max(sum(d["SQ_WAVES"]), 1)
         flops = per_wave * nw * MFMA_FLOPS
         t = statistics.mean(next(v for kk, v in dur.items() if kk.startswith(k) or kk.startswith("void " + k)))
-        print("| %s | %d | %.1f | %.3g | %.1f | %.1f | %.1f |" % (short(full[0]), nw, per_wave, flops, t * 1e6,
-                                                                 flops / t / 1e12, 100 * flops / t / FP32_MFMA_PEAK))
+        busy = sum(d["SQ_VALU_MFMA_BUSY_CYCLES"]) / (SIMDS_PER_ENGINE * sum(d["SQ_BUSY_CYCLES"]))
+        print("| %s | %d | %.1f | %.3g | %.1f | %.1f | %.1f | %.1f |"
+              % (short(full[0]), nw, per_wave, flops, t * 1e6, flops / t / 1e12, 100 * flops / t / FP32_MFMA_PEAK,
+                 100 * busy))
 
 
 def per_dispatch_bytes(fdb, wdb):
