@@ -127,10 +127,6 @@ def test_fallback_control_round_trips():
     assert mb.memoroid_testing_set_fallback_polls(-1) == 4096
 
 
-def _up(n):
-    return -(-n // 256) * 256
-
-
 def test_workspace_queries():
     f = mb.memoroid_scan_diag_workspace_bytes
     assert f(1, 1 << 20, 256, mb.F32, mb.F32) > 0
@@ -151,16 +147,6 @@ def test_workspace_queries():
     hb = mb.memoroid_scan_linattn_bwd_workspace_bytes
     assert h(1 << 20, 251, 64, 64, 64) > 0 and hb(1 << 20, 251, 64, 64, 64) > 0
     assert h(64, 252, 64, 64, 64) == 0 and hb(64, 252, 64, 64, 64) == 0
-    # the workgroups of a call (segments of c chunks and heads) fill the rounds
-    # that 256 CUs take them in: no CU has more than 1.15 times its share (with
-    # the longest segments that leave 512 workgroups these have 1.31 to 1.36)
-    for T, H in ((18000, 8), (25000, 8), (36000, 4), (49152, 3), (100000, 2)):
-        seg = [s for s in range(1, T // 64 + 2)
-               if h(T, H, 64, 64, 64) == 256 + _up(8 * s) + _up(s * H * 4160 * 4) + _up(s)]
-        n = -(-T // 64)
-        assert len(seg) == 1, (T, H, seg)
-        c = min(c for c in range(1, 9) if -(-n // c) == seg[0])
-        assert -(-seg[0] * H // 256) * c <= 1.15 * n * H / 256, (T, H, c)
     # descriptor storage grows linearly in T
     assert f(1, 1 << 21, 256, mb.F32, mb.F32) < 2.2 * f(1, 1 << 20, 256, mb.F32, mb.F32)
 
@@ -211,6 +197,37 @@ def test_diag_bwd_validation():
     assert bwd(a_stride_t=2) == mb.EINVAL
     assert bwd(workspace=None) == mb.EWORKSPACE
     assert bwd(workspace_bytes=16) == mb.EWORKSPACE
+
+
+def _segments(T, H):
+    """Segments of a linear-attention call, from its workspace size."""
+    def up(n):
+        return -(-n // 256) * 256
+    size = mb.memoroid_scan_linattn_workspace_bytes(T, H, 64, 64, 64)
+    n = [s for s in range(1, T // 64 + 2) if size == 256 + up(8 * s) + up(s * H * 4160 * 4) + up(s)]
+    assert len(n) == 1, (T, H, n)
+    return n[0]
+
+
+@pytest.mark.parametrize("T,H", [(18000, 8), (25000, 8), (36000, 4), (49152, 3), (100000, 2)])
+def test_linattn_segments_fill_the_cus(T, H):
+    """The workgroups of a call (segments of c chunks and heads) fill the rounds
+    that 256 CUs take them in: no CU has more than 1.15 times its share (with the
+    longest segments that leave 512 workgroups these have 1.31 to 1.36)."""
+    n, seg = -(-T // 64), _segments(T, H)
+    c = min(c for c in range(1, 9) if -(-n // c) == seg)
+    assert -(-seg * H // 256) * c <= 1.15 * n * H / 256, c
+
+
+def test_linattn_segments_of_the_gpu_tests():
+    """The segments that the GPU tests of linear attention are there for: just
+    past what 2, 4, 8 and 16 segments per thread of the state scan take at once,
+    up to and past what readers add up themselves, of one to eight chunks."""
+    for T, H, seg in ((64 * 65, 1, 65), (64 * 129, 1, 129), (64 * 257 - 3, 1, 257), (64 * 1026, 1, 206),
+                      (64 * 1026 + 13, 4, 172), (64 * 513, 1, 513), (64 * 1021 - 51, 4, 128), (64 * 4100 - 3, 1, 684),
+                      (64 * 12 + 9, 2, 13), (2048 - 13, 32, 16), (2048 + 17, 64, 11), (1024 - 5, 64, 8), (1024, 64, 8),
+                      (64 * 8, 2, 8), (64 * 8 + 1, 2, 9), (262144, 1, 512)):
+        assert _segments(T, H) == seg, (T, H)
 
 
 def test_linattn_validation():

@@ -62,12 +62,14 @@ def test_head_counts(H):
     check(tapes.make_linattn(3, seed=400 + H, T=1000 + 13 * H, H=H), "heads")
 
 
-@pytest.mark.parametrize("T,H", [(64 * 65, 1), (64 * 129, 1), (64 * 257 - 3, 1), (64 * 1026, 1), (64 * 1026 + 13, 4)])
+@pytest.mark.parametrize("T,H", [(64 * 65, 1), (64 * 129, 1), (64 * 257 - 3, 1), (64 * 1026, 1), (64 * 1026 + 13, 4),
+                                 (64 * 513, 1), (64 * 1021 - 51, 4), (64 * 4100 - 3, 1)])
 def test_segment_lengths_and_scan_rounds(T, H):
     """Segments of one chunk in numbers just past what 2, 4 and 8 segments per
-    thread of the state scan take at once (65, 129, 257), 513 segments of two
-    chunks (two rounds of the scan, carried over), and segments of eight
-    chunks, the last of them short."""
+    thread of the state scan take at once (65, 129, 257), 206 segments of five
+    chunks and 172 of six, the last of them short, 513 of one chunk (two rounds
+    of the scan, carried over), 128 of eight chunks and 684 of six (two
+    rounds), the last short."""
     check(tapes.make_linattn(3, seed=500 + H, T=T, H=H), "segments")
 
 
